@@ -42,7 +42,7 @@ __device__ __forceinline__ void sweep3d_body(const Sweep3DArgs& a, const CoefPac
   constexpr int C1 = B1 - 2 * BT * R;
   constexpr int LO2 = overlap_left(BT, R, sizeof(T));  // column overlap on the left
   constexpr int C2 = compute_width(B2, BT, R, sizeof(T));
-  constexpr bool WHOLE = LO2 % CPL == 0 && C2 % CPL == 0;  // compute columns are whole lanes
+  constexpr int LK = LO2 % CPL;      // cell of its lane at which the compute columns start
   constexpr int XR = M + 2 * R;      // extended rows: R from wave w-1 | own M | R from wave w+1
   constexpr int XL = CPL + 2 * R;    // extended columns
   constexpr uint32_t WB = sizeof(T);
@@ -56,26 +56,22 @@ __device__ __forceinline__ void sweep3d_body(const Sweep3DArgs& a, const CoefPac
   const int pl_a = R + chunk * a.chunk;        // output planes of this stream block
   const int pl_b = min(pl_a + a.chunk, I0 + R);
 
-  // per-row store validity (wave-uniform) and per-cell column masks
+  // per-row store validity and boundary rows (wave-uniform)
   bool row_st[M], row_hal[M];
   sfor<M>([&](auto MI) S5D_INL {
     const int i = row0 + MI;
     row_st[MI] = i >= r_first && i < r_first + C1 && i < I1 + R;
     row_hal[MI] = i < R || i >= I1 + R;
   });
-  uint32_t soff[CPL], loff[CPL];
+  // lanes from c_first on store their cells as one vector that the row
+  // descriptor cuts off at the end of the compute columns; a lane in which they
+  // start stores its last CPL - LK cells
+  const uint32_t st_bytes = static_cast<uint32_t>(min(c_first + C2, I2 + R)) * WB;
+  const uint32_t vstore = colL >= c_first ? static_cast<uint32_t>(colL) * WB : kOutOfRange;
+  const uint32_t lstore = colL == c_first - LK ? static_cast<uint32_t>(c_first) * WB : kOutOfRange;
+  const uint32_t loff = static_cast<uint32_t>(colL) * WB;  // EDGE loads (negative columns are out of range)
   bool hcol[CPL];
-  bool full = true;
-  sfor<CPL>([&](auto K) S5D_INL {
-    const int col = colL + K;
-    const bool st = col >= c_first && col < c_first + C2 && col < I2 + R;
-    full = full && st;
-    soff[K] = st ? static_cast<uint32_t>(col) * WB : kOutOfRange;
-    loff[K] = (col >= 0 && col < P2) ? static_cast<uint32_t>(col) * WB : kOutOfRange;
-    hcol[K] = col < R || col >= I2 + R;
-  });
-  const uint32_t vstore = full ? static_cast<uint32_t>(colL) * WB : kOutOfRange;
-  if (full) sfor<CPL>([&](auto K) S5D_INL { soff[K] = kOutOfRange; });
+  sfor<CPL>([&](auto K) S5D_INL { hcol[K] = colL + K < R || colL + K >= I2 + R; });
 
   const T* __restrict__ src = static_cast<const T*>(a.src);
   T* __restrict__ dst = static_cast<T*>(a.dst);
@@ -89,11 +85,9 @@ __device__ __forceinline__ void sweep3d_body(const Sweep3DArgs& a, const CoefPac
       if constexpr (EDGE) {
         const bool in = p < P0 && i >= 0 && i < P1;
         const auto rs = make_rsrc(row_ptr(src, in ? p : 0, in ? i : 0), in ? static_cast<uint32_t>(P2) * WB : 0u);
-        sfor<CPL>([&](auto K) S5D_INL {
-          T t;
-          buf_load(t, rs, loff[K]);
-          v[MI][+K] = t;
-        });
+        T t[CPL];
+        buf_load_lane(t, rs, loff);
+        sfor<CPL>([&](auto K) S5D_INL { v[MI][+K] = t[K]; });
       } else {
         const LaneVec<T, CPL> lv = *reinterpret_cast<const LaneVec<T, CPL>*>(row_ptr(src, min(p, P0 - 1), i) + colL);
         sfor<CPL>([&](auto K) S5D_INL { v[MI][+K] = lv.v[K]; });
@@ -276,10 +270,9 @@ __device__ __forceinline__ void sweep3d_body(const Sweep3DArgs& a, const CoefPac
           sfor<M>([&](auto MI) S5D_INL {
             const bool keep = keep_pl && row_st[MI];
             const auto rs = make_rsrc(row_ptr(dst, keep ? o : pl_a, keep ? row0 + MI : r_first),
-                                      keep ? static_cast<uint32_t>(P2) * WB : 0u);
-            buf_store_lane(out[MI], rs, vstore);
-            // lanes straddling the compute region's edge store cell by cell
-            if constexpr (EDGE || !WHOLE) sfor<CPL>([&](auto K) S5D_INL { buf_store(out[MI][K], rs, soff[K]); });
+                                      keep ? st_bytes : 0u);
+            buf_store_cells<0>(out[MI], rs, vstore);
+            if constexpr (LK != 0) buf_store_cells<LK>(out[MI], rs, lstore);
           });
         }
       });

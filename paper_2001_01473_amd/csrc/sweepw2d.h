@@ -18,7 +18,7 @@
 // neighbours in another lane come from DPP whole-wave shifts.  The paper
 // keeps the 1+2R rows of the "Otherwise" case in shared memory; here they
 // never leave the registers and the tile needs no LDS except the EDGE waves'
-// stash of boundary columns (as in the associative sweep).
+// ring of boundary cells (as in the associative sweep).
 //
 // Operations (OP):
 //  OP_GRADIENT (star, R = 1): out = cc*f + 1/sqrt(c0 + sum_n (f - f_n)^2)
@@ -58,8 +58,7 @@ __device__ __forceinline__ void sweepw2d_body(const SweepW2DArgs& wa, const WinC
   constexpr int W = 64 * CPL;
   constexpr int LO = overlap_left(BT, R, sizeof(T));
   constexpr int C = compute_width(W, BT, R, sizeof(T));
-  constexpr bool WHOLE = LO % CPL == 0 && C % CPL == 0;
-  constexpr int MCOL = BT * R + 1;
+  constexpr int MROW = BT * R + 1;
   constexpr int XL = CPL + 2 * R;
   constexpr int NP = npts(2, R, BOX);
   constexpr uint32_t WB = sizeof(T);
@@ -72,34 +71,15 @@ __device__ __forceinline__ void sweepw2d_body(const SweepW2DArgs& wa, const WinC
   const int col0 = c_first - LO;
   const int colL = col0 + lane * CPL;
 
-  uint32_t soff[CPL];
-  bool full = true;
-  sfor<CPL>([&](auto K) S5D_INL {
-    const int col = colL + K;
-    const bool st = col >= c_first && col < c_first + C && col < I1 + R;
-    full = full && st;
-    soff[K] = st ? static_cast<uint32_t>(col) * WB : kOutOfRange;
-  });
-  const uint32_t vstore = full ? static_cast<uint32_t>(colL) * WB : kOutOfRange;
-  if (full) sfor<CPL>([&](auto K) S5D_INL { soff[K] = kOutOfRange; });
-  uint32_t loff[CPL];
+  // stores, EDGE loads and boundary columns as in the associative sweep
+  constexpr int LK = LO % CPL;
+  const uint32_t st_bytes = static_cast<uint32_t>(min(c_first + C, I1 + R)) * WB;
+  const uint32_t vstore = colL >= c_first ? static_cast<uint32_t>(colL) * WB : kOutOfRange;
+  const uint32_t lstore = colL == c_first - LK ? static_cast<uint32_t>(c_first) * WB : kOutOfRange;
+  const uint32_t loff = static_cast<uint32_t>(colL) * WB;
   bool hcol[CPL];
-  int hl = -1;
-  if constexpr (EDGE) {
-    bool left = false, right = false;
-    sfor<CPL>([&](auto K) S5D_INL {
-      const int col = colL + K;
-      loff[K] = (col >= 0 && col < P1) ? static_cast<uint32_t>(col) * WB : kOutOfRange;
-      const bool l = col >= 0 && col < R, r = col >= I1 + R && col < P1;
-      hcol[K] = l || r;
-      left |= l;
-      right |= r;
-    });
-    const int lL = (0 - col0) / CPL;
-    const int lR = (I1 + R - col0) / CPL;
-    if (left) hl = lane - lL;
-    else if (right) hl = 2 + lane - lR;
-  }
+  if constexpr (EDGE)
+    sfor<CPL>([&](auto K) S5D_INL { hcol[K] = colL + K < R || colL + K >= I1 + R; });
   // weight-field columns: interior column col - R of each row
   uint32_t foff[CPL];
   if constexpr (OP == OP_VARCOEF)
@@ -114,9 +94,9 @@ __device__ __forceinline__ void sweepw2d_body(const SweepW2DArgs& wa, const WinC
 
   auto load_row = [&](T (&v)[CPL], int row) S5D_INL {
     if constexpr (EDGE) {
-      const auto rs = make_rsrc(src + static_cast<int64_t>(min(row, P0)) * P1,
+      const auto rs = make_rsrc(src + static_cast<int64_t>(min(row, P0 - 1)) * P1,
                                 row < P0 ? static_cast<uint32_t>(P1) * WB : 0u);
-      sfor<CPL>([&](auto K) S5D_INL { buf_load(v[K], rs, loff[K]); });
+      buf_load_lane(v, rs, loff);
     } else {
       const T* rp = src + static_cast<int64_t>(min(row, P0 - 1)) * P1 + colL;
       const LaneVec<T, CPL> lv = *reinterpret_cast<const LaneVec<T, CPL>*>(rp);
@@ -155,14 +135,13 @@ __device__ __forceinline__ void sweepw2d_body(const SweepW2DArgs& wa, const WinC
     });
   };
 
+  int srow = s0 % MROW;  // ring slot of row s, stepped along with s
   auto iteration = [&](const int sb) S5D_INL {
     sfor<NS>([&](auto PH) S5D_INL {
       const int s = sb + PH;
       load_vec(ringv[pmod(PH - 1, NR)], s + NR - 1);
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (EDGE) {
-        if (hl >= 0) sfor<CPL>([&](auto K) S5D_INL { stash->cols[s % MCOL][hl][K] = ringv[PH % NR][+K]; });
-      }
+      if constexpr (EDGE) sfor<CPL>([&](auto K) S5D_INL { stash->rows[srow][lane][K] = ringv[PH % NR][+K]; });
       T cur[CPL];
       sfor<CPL>([&](auto K) S5D_INL { cur[K] = ringv[PH % NR][+K]; });
 
@@ -233,13 +212,10 @@ __device__ __forceinline__ void sweepw2d_body(const SweepW2DArgs& wa, const WinC
 #undef S5D_WSLOT
 
         if constexpr (EDGE && lv < BT) {
-          if (o < R || o >= I0 + R) {
-            if (o >= 0 && o < P0) load_row(out, o);
-          } else {
-            const LaneVec<T, CPL> hv = *reinterpret_cast<const LaneVec<T, CPL>*>(
-                stash->cols[o % MCOL][hl < 0 ? 0 : hl]);
-            sfor<CPL>([&](auto K) S5D_INL { out[K] = hcol[K] ? hv.v[K] : out[K]; });
-          }
+          const int os = srow - lv * R;  // ring slot of row o
+          const bool rowb = o < R || o >= I0 + R;
+          const LaneVec<T, CPL> hv = *reinterpret_cast<const LaneVec<T, CPL>*>(stash->rows[os < 0 ? os + MROW : os][lane]);
+          sfor<CPL>([&](auto K) S5D_INL { out[K] = (rowb || hcol[K]) ? hv.v[K] : out[K]; });
         }
 
         if constexpr (lv < BT) {
@@ -247,11 +223,12 @@ __device__ __forceinline__ void sweepw2d_body(const SweepW2DArgs& wa, const WinC
         } else {
           const bool keep = o >= row_a && o < row_b;
           const auto rs = make_rsrc(dst + static_cast<int64_t>(keep ? o : row_a) * P1,
-                                    keep ? static_cast<uint32_t>(P1) * WB : 0u);
-          buf_store_lane(out, rs, vstore);
-          if constexpr (EDGE || !WHOLE) sfor<CPL>([&](auto K) S5D_INL { buf_store(out[K], rs, soff[K]); });
+                                    keep ? st_bytes : 0u);
+          buf_store_cells<0>(out, rs, vstore);
+          if constexpr (LK != 0) buf_store_cells<LK>(out, rs, lstore);
         }
       });
+      if constexpr (EDGE) srow = srow + 1 == MROW ? 0 : srow + 1;
     });
   };
   iteration(s0);
