@@ -154,7 +154,13 @@ s5d_status s5d_plan_create(const s5d_desc *desc, const s5d_tuning *tuning, s5d_p
 void s5d_plan_destroy(s5d_plan *plan);
 
 /* The blocking parameters the plan uses (`chosen`, may be NULL) and the
- * size in bytes of one padded grid buffer (`bytes_per_buffer`, may be NULL). */
+ * size in bytes of one padded grid buffer (`bytes_per_buffer`, may be NULL).
+ * A 2D plan whose blocking is left to the library may run a sweep on resident
+ * tiles instead (a workgroup keeps a whole tile in registers and advances it
+ * several steps per launch) where its estimate says that is faster: small and
+ * mid-sized grids, alone, in a batch or served.  The result has the same
+ * bits.  The parameters returned are then those of the plan's streaming
+ * kernels, which persistent batches and the performance model use. */
 s5d_status s5d_plan_query(const s5d_plan *plan, s5d_tuning *chosen, int64_t *bytes_per_buffer);
 
 /* Run the whole sweep of `plan` on device buffers.

@@ -41,10 +41,11 @@ DEVICE_FLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC",
                 "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                 "-I" + CSRC, "-I" + INCLUDE]
 
-HOST_SOURCES = ["abi.cpp", "batch.cpp", "server.cpp", "tune.cpp", "halo.hip", "norms.hip", "direct.hip"]
+HOST_SOURCES = ["abi.cpp", "batch.cpp", "server.cpp", "tune.cpp", "halo.hip", "norms.hip", "direct.hip", "tile2d.hip"]
 HEADERS = ["s5d_internal.h", "kcommon.h", "sweep2d.h", "sweep3d.h", "sweepw2d.h", "sweepp2d.h", "persist2d.h",
            "persist_schedule.h"]
-HOST_HEADERS = ["host.h", "batch.h", "norms.h", "direct.h", "stream2d.h", "stream3d.h"]  # not included by the variant units
+HOST_HEADERS = ["host.h", "batch.h", "norms.h", "direct.h", "stream2d.h", "stream3d.h", "tile.h", "tile2d.h",
+                "gradient.h"]  # not included by the variant units
 
 # Kernel kinds: (name, C++ type, 32-bit words per element, accumulation
 # policy).  Kind 2 is float32 with compensated (Dot2) accumulation.
@@ -395,7 +396,7 @@ def build(jobs: int | None = None, incremental: bool = False, verbose: bool = Fa
     base_hdr = ["s5d_internal.h", "kcommon.h"]
     unit_hdr = {
         "2d": _digest([os.path.join(CSRC, h) for h in base_hdr + ["sweep2d.h"]], []),
-        "w2d": _digest([os.path.join(CSRC, h) for h in base_hdr + ["sweep2d.h", "sweepw2d.h"]], []),
+        "w2d": _digest([os.path.join(CSRC, h) for h in base_hdr + ["sweep2d.h", "sweepw2d.h", "gradient.h"]], []),
         "3d": _digest([os.path.join(CSRC, h) for h in base_hdr + ["sweep3d.h"]], []),
         "p2d": _digest([os.path.join(CSRC, h) for h in base_hdr + ["sweep2d.h", "sweepp2d.h", "persist2d.h",
                                                                      "persist_schedule.h"]], []),
@@ -416,8 +417,9 @@ def build(jobs: int | None = None, incremental: bool = False, verbose: bool = Fa
     host = [os.path.join(CSRC, s) for s in HOST_SOURCES]
     host_hdr = hdr + _digest([os.path.join(CSRC, h) for h in HOST_HEADERS] +
                              [os.path.join(INCLUDE, "stencil5d.h")], [])
-    # longest first: the box and deep variants dominate the build time
-    order = sorted(units, key=lambda p: ("kp2d_" not in p, "box" not in p, -len(p))) + host
+    # longest first: the direct and tile kernels of the host sources, then the
+    # box and deep variants dominate the build time
+    order = host + sorted(units, key=lambda p: ("kp2d_" not in p, "box" not in p, -len(p)))
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
         futs = {ex.submit(_compile, s, host_hdr if s in host else key_of_unit(s), incremental): s
                 for s in order}

@@ -349,6 +349,7 @@ s5d_status plan_2d(s5d_plan* p, const s5d_tuning& req, int box, int r) {
     const DeviceInfo dev = query_device();
     int occ = dev.ok ? p->by_bt[bt].occupancy() : 0;
     if (occ <= 0) occ = 2;
+    p->cus = dev.cus;
     p->slots = static_cast<int64_t>(dev.cus) * occ * s5d::kWavesPerBlock;
   }
   if (chunk == 0) {
@@ -442,6 +443,103 @@ std::vector<int> plan_rounds(const s5d_plan* p) {
 }
 
 namespace {
+
+// Estimates of a 2D sweep in microseconds when it gets `share` of the machine,
+// compared with each other to choose its kernels and never reported.  A
+// round pays kRoundUs for its launch, first loads and last stores; the rest is
+// vector issue at 4 clocks an instruction and SIMD and, for tiles, memory.
+//
+// A tile loads, computes and stores in turn, so its bytes cost time on top of
+// the issue (16 TB/s while both buffers stay in the 256 MB last-level cache),
+// and a round is never faster than 5 TB/s once they do not (both measured:
+// float64 5-point star 2048^2, 80 MB a round, 4.6 us over the issue; 8000^2,
+// 1.1 GB a round, 225 us).  The streaming estimate is scaled to measured times
+// (float32 by 0.75, float64 by 0.9: within 25 % for the plain stencils from
+// 2048^2 to 8000^2); on small grids it is up to two times too low, where
+// tiles are three to five times faster anyway.
+constexpr double kRoundUs = 5.0;
+constexpr double kClocksPerUs = 2400.0;
+
+double tile_us(const s5d_plan* p, const TileKernel2D& k, int bt, int64_t n_rounds, double share) {
+  const int r = p->d.radius;
+  const int64_t c0 = k.rows - 2LL * bt * r, c1 = compute_width(k.cols, bt, r, p->elem);
+  const double tiles = static_cast<double>((p->d.interior[0] + c0 - 1) / c0) *
+                       static_cast<double>((p->d.interior[1] + c1 - 1) / c1);
+  // tiles each CU works through; few tiles leave the fullest CU one more
+  double per_cu = tiles / (p->cus * share);
+  per_cu = per_cu <= 1.0 ? 1.0 : (per_cu < 4.0 ? std::ceil(per_cu) : per_cu + 0.5);
+  const double step = 0.06 + per_cu * k.step_clocks / kClocksPerUs;  // + exchange and barrier
+  const double bytes = tiles * k.rows * k.cols * p->elem + static_cast<double>(p->bytes);
+  double round = bt * step + bytes / (16e6 * share);
+  if (2 * p->bytes > 200e6) round = std::max(round, bytes / (5e6 * share));
+  return static_cast<double>(n_rounds) * (kRoundUs + round);
+}
+
+double own_us(const s5d_plan* p, double share) {
+  const int r = p->d.radius, bt = p->tun.bt;
+  const double cells = static_cast<double>(p->d.interior[0]) * static_cast<double>(p->d.interior[1]);
+  const double T = static_cast<double>(p->d.steps);
+  const double terms = p->expr == EXPR_GRADIENT ? 38 : npts(2, r, p->d.shape == S5D_BOX) *
+                                                               (p->kind == KIND_F32_COMP ? 8.0 : 1.0) +
+                                                           (p->expr == EXPR_DIV ? 8 : 0);
+  // one step per launch (the compensated stencils but the 5-point star)
+  if (p->direct) return T * (kRoundUs + 2.5 + cells * terms / 64 / (p->cus * share) / kClocksPerUs);
+  const int cpl = p->tun.cells_per_lane;
+  const double slots = std::max(1.0, static_cast<double>(p->slots) * share);
+  const int64_t c1 = compute_width(64 * cpl, bt, r, p->elem);
+  const double ntiles = static_cast<double>((p->d.interior[1] + c1 - 1) / c1);
+  const int64_t h = share < 1.0 ? shared_chunk(p, bt, share) : p->tun.stream_chunk;
+  const double blocks = ntiles * static_cast<double>((p->d.interior[0] + h - 1) / h);
+  const double turns = std::max(blocks / slots, 1.0) + (blocks > slots ? kTail : 0.35);
+  // waves sharing a SIMD
+  const double waves = std::max(1.0, std::min(static_cast<double>(p->slots), blocks / share) / (4.0 * p->cus));
+  const double row = (cpl * terms + 2 * r * (p->elem / 4) + 4) * 4 * waves * 1.15 / kClocksPerUs;
+  const double round = std::max(turns * static_cast<double>(h + 2LL * bt * r) * bt * row,
+                                2.5 * static_cast<double>(p->bytes) / (5e6 * share));
+  return std::ceil(T / bt) * (kRoundUs + round) * (p->elem == 4 ? 0.75 : 0.9);
+}
+
+}  // namespace
+
+Rounds tile_rounds(const s5d_plan* p, double share, double* us) {
+  Rounds out;
+  *us = 1e300;
+  const int64_t T = p->d.steps;
+  if (!p->tile_ok || T <= 0) return out;
+  int64_t n_best = 1;
+  for (int shape = 0; shape < kTileShapes2D; ++shape) {
+    const TileKernel2D* k = tile_kernel2d(p->kind, p->expr, p->d.radius, p->d.shape == S5D_BOX, shape);
+    for (int bt = 1; bt <= 20 && k->rows - 2 * bt * p->d.radius >= 8 &&
+                     compute_width(k->cols, bt, p->d.radius, p->elem) >= 16; ++bt) {
+      // rounds of nearly equal depth, as many as T's parity asks for
+      int64_t n = (T + bt - 1) / bt;
+      if ((n ^ T) & 1) ++n;
+      const double t = tile_us(p, *k, static_cast<int>((T + n - 1) / n), n, share);
+      if (t < *us) {
+        *us = t;
+        n_best = n;
+        out.tile = k;
+      }
+    }
+  }
+  out.bt.reserve(static_cast<size_t>(n_best));
+  const int64_t q = T / n_best, rem = T % n_best;
+  for (int64_t i = 0; i < n_best; ++i) out.bt.push_back(static_cast<int>(q + (i < rem ? 1 : 0)));
+  return out;
+}
+
+double own_rounds_us(const s5d_plan* p, double share) { return p->tile_ok ? own_us(p, share) : 0.0; }
+
+Rounds choose_rounds(const s5d_plan* p, double share) {
+  double us = 0;
+  Rounds out = tile_rounds(p, share, &us);
+  if (out.tile && us < 0.95 * own_us(p, share)) return out;
+  out.tile = nullptr;
+  out.bt = plan_rounds(p);
+  return out;
+}
+
+namespace {
 Round2D round2d(const s5d_plan* p, const void* src, void* dst, hipStream_t stream, const void* fields = nullptr) {
   Round2D rd;
   rd.fields = fields;
@@ -470,18 +568,22 @@ Round3D round3d(const s5d_plan* p, const void* src, void* dst, hipStream_t strea
 }
 }  // namespace
 
-hipError_t launch_round(const s5d_plan* p, int bt, const void* src, void* dst, hipStream_t stream,
-                        const void* fields) {
+hipError_t launch_round(const s5d_plan* p, const TileKernel2D* tile, int bt, const void* src, void* dst,
+                        hipStream_t stream, const void* fields) {
+  if (tile) return tile->launch(round2d(p, src, dst, stream), bt);
   if (p->d.ndim == 3) return p->by_bt3[bt].launch(round3d(p, src, dst, stream));
   return p->by_bt[bt].launch(round2d(p, src, dst, stream, fields));
 }
 
-BatchHooks batch_hooks(const s5d_plan* p, int bt) {
+BatchHooks batch_hooks(const s5d_plan* p, const TileKernel2D* tile, int bt) {
+  if (tile) return BatchHooks{tile->launch_batch, tile->item_bytes};
   if (p->d.ndim == 3) return BatchHooks{p->by_bt3[bt].launch_batch, p->by_bt3[bt].item_bytes};
   return BatchHooks{p->by_bt[bt].launch_batch, p->by_bt[bt].item_bytes};
 }
 
-int fill_round_item(const s5d_plan* p, int bt, const void* src, void* dst, void* item, int chunk) {
+int fill_round_item(const s5d_plan* p, const TileKernel2D* tile, int bt, const void* src, void* dst, void* item,
+                    int chunk) {
+  if (tile) return tile->fill_item(item, round2d(p, src, dst, nullptr), bt);
   if (p->d.ndim == 3) {
     Round3D rd = round3d(p, src, dst, nullptr);
     if (chunk > 0) rd.chunk = chunk;
@@ -646,6 +748,7 @@ s5d_status s5d_plan_create(const s5d_desc* desc, const s5d_tuning* tuning, s5d_p
   // is taken if one is cached and still valid; else the library's defaults
   s5d_tuning cached;
   s5d_status st = S5D_EINVAL;
+  bool from_cache = false;
   s5d::load_default_tuning();
   if (!tuning && s5d::tune_cache_lookup(d, &cached)) {
     st = d.ndim == 2 ? plan_2d(p, cached, box, r) : plan_3d(p, cached, box, r);
@@ -656,6 +759,7 @@ s5d_status s5d_plan_create(const s5d_desc* desc, const s5d_tuning* tuning, s5d_p
       // the library chose it (through the tuner), not the caller: batches and
       // servers may still size the stream blocks for a grid's share
       p->chunk_auto = true;
+      from_cache = true;
     }
   }
   const bool no_blocking = req.bt <= 1 && req.cells_per_lane == 0 && req.rows_per_wave == 0 && req.tile0 == 0 &&
@@ -687,6 +791,9 @@ s5d_status s5d_plan_create(const s5d_desc* desc, const s5d_tuning* tuning, s5d_p
     }
   }
   if (st == S5D_OK) p->tun.kernel = p->direct ? S5D_KERNEL_DIRECT : S5D_KERNEL_BLOCKED;
+  p->tile_ok = d.ndim == 2 && !from_cache && req.kernel == S5D_KERNEL_AUTO && no_blocking && req.bt == 0 &&
+               s5d::tile_kernel2d(p->kind, p->expr, r, box != 0, 0) != nullptr;
+  if (p->tile_ok && p->direct) p->cus = query_device().cus;
   if (st != S5D_OK) {
     delete p;
     return st;
@@ -733,9 +840,9 @@ s5d_status s5d_run_fields(const s5d_plan* plan, void* buf0, void* buf1, const vo
   hipError_t e = s5d::launch_boundary_copy(plan, buf0, buf1, st);
   if (e != hipSuccess) return device_fail(e, "boundary copy launch");
   void* bufs[2] = {buf0, buf1};
-  const std::vector<int> rounds = s5d::plan_rounds(plan);
-  for (size_t k = 0; k < rounds.size(); ++k) {
-    e = s5d::launch_round(plan, rounds[k], bufs[k % 2], bufs[(k + 1) % 2], st, fields);
+  const s5d::Rounds rounds = s5d::choose_rounds(plan, 1.0);
+  for (size_t k = 0; k < rounds.bt.size(); ++k) {
+    e = s5d::launch_round(plan, rounds.tile, rounds.bt[k], bufs[k % 2], bufs[(k + 1) % 2], st, fields);
     if (e != hipSuccess) return device_fail(e, "sweep launch");
   }
   return S5D_OK;

@@ -35,7 +35,7 @@ s5d_status build_step(const std::vector<RoundItem>& items, std::vector<unsigned 
   std::vector<LaunchBatchFn> order;
   std::map<LaunchBatchFn, std::vector<size_t>> groups;
   for (size_t i = 0; i < items.size(); ++i) {
-    const BatchHooks h = batch_hooks(items[i].plan, items[i].bt);
+    const BatchHooks h = batch_hooks(items[i].plan, items[i].tile, items[i].bt);
     if (!h.launch) return fail(S5D_EUNSUPPORTED, "kernel variant without a batched entry point");
     auto it = groups.find(h.launch);
     if (it == groups.end()) {
@@ -48,7 +48,7 @@ s5d_status build_step(const std::vector<RoundItem>& items, std::vector<unsigned 
   std::vector<unsigned char> scratch;
   for (LaunchBatchFn fn : order) {
     const std::vector<size_t>& members = groups[fn];
-    const int item_bytes = batch_hooks(items[members[0]].plan, items[members[0]].bt).item_bytes;
+    const int item_bytes = batch_hooks(items[members[0]].plan, items[members[0]].tile, items[members[0]].bt).item_bytes;
     GroupLaunch g;
     g.fn = fn;
     g.items_off = align_up(blob.size(), 256);
@@ -59,7 +59,7 @@ s5d_status build_step(const std::vector<RoundItem>& items, std::vector<unsigned 
       // write through an aligned temporary: blob may reallocate below
       scratch.assign(static_cast<size_t>(item_bytes) + 16, 0);
       void* tmp = reinterpret_cast<void*>(align_up(reinterpret_cast<uintptr_t>(scratch.data()), 16));
-      nblk[j] = fill_round_item(ri.plan, ri.bt, ri.src, ri.dst, tmp, ri.chunk);
+      nblk[j] = fill_round_item(ri.plan, ri.tile, ri.bt, ri.src, ri.dst, tmp, ri.chunk);
       if (nblk[j] <= 0) return fail(S5D_EUNSUPPORTED, "grid too large for one launch");
       std::memcpy(blob.data() + g.items_off + j * static_cast<size_t>(item_bytes), tmp,
                   static_cast<size_t>(item_bytes));
@@ -411,7 +411,6 @@ s5d_status s5d_batch_create(const s5d_plan* const* plans, void* const* buf0, voi
       b->result_index[g] = static_cast<int32_t>(p->d.steps % 2);
       if (p->dcoef) b->coef_tables.push_back(p->dcoef);
       rounds[g] = s5d::plan_rounds(p);
-      kmax = std::max(kmax, rounds[g].size());
       if (!rounds[g].empty()) {
         s5d::HaloItem h;
         h.src = buf0[g];
@@ -439,9 +438,35 @@ s5d_status s5d_batch_create(const s5d_plan* const* plans, void* const* buf0, voi
       work[g] = static_cast<double>(plans[g]->d.steps) * static_cast<double>(plans[g]->bytes / plans[g]->elem);
       total_work += work[g];
     }
+    // Resident tiles for all the grids that may run on them, or for none: the
+    // rounds of one index wait for each other, so a batch lasts as long as its
+    // slowest grid (24 float32 stars of 256 to 2048 cells a side: 6.4 ms on
+    // their own kernels, 6.6 mixed by each grid's own estimate).
+    // Plans whose own kernels cannot be batched stay refused.
+    std::vector<const s5d::TileKernel2D*> tiles(static_cast<size_t>(n), nullptr);
+    if (!b->persistent && total_work > 0) {
+      std::vector<s5d::Rounds> on_tiles(static_cast<size_t>(n));
+      double tile_us = 0, own_us = 0;
+      for (int32_t g = 0; g < n; ++g) {
+        if (rounds[g].empty() || !s5d::batch_hooks(plans[g], nullptr, plans[g]->tun.bt).launch) continue;
+        double us = 0;
+        on_tiles[g] = s5d::tile_rounds(plans[g], work[g] / total_work, &us);
+        if (!on_tiles[g].tile) continue;
+        tile_us = std::max(tile_us, us);
+        own_us = std::max(own_us, s5d::own_rounds_us(plans[g], work[g] / total_work));
+      }
+      if (tile_us < own_us)
+        for (int32_t g = 0; g < n; ++g)
+          if (on_tiles[g].tile) {
+            rounds[g] = std::move(on_tiles[g].bt);
+            tiles[g] = on_tiles[g].tile;
+          }
+    }
     for (int32_t g = 0; g < n; ++g)
-      if (!rounds[g].empty() && total_work > 0)
+      if (!rounds[g].empty() && total_work > 0 && !tiles[g])
         chunks[g] = s5d::shared_chunk(plans[g], plans[g]->tun.bt, work[g] / total_work);
+    kmax = 0;
+    for (int32_t g = 0; g < n; ++g) kmax = std::max(kmax, rounds[g].size());
     std::vector<unsigned char> blob;
     if (!halos.empty()) {
       b->halo_off = 0;
@@ -462,7 +487,7 @@ s5d_status s5d_batch_create(const s5d_plan* const* plans, void* const* buf0, voi
       for (int32_t g = 0; g < n; ++g) {
         if (k >= rounds[g].size()) continue;
         void* bufs[2] = {buf0[g], buf1[g]};
-        items.push_back(s5d::RoundItem{plans[g], rounds[g][k], bufs[k % 2], bufs[(k + 1) % 2], chunks[g]});
+        items.push_back(s5d::RoundItem{plans[g], tiles[g], rounds[g][k], bufs[k % 2], bufs[(k + 1) % 2], chunks[g]});
       }
       const s5d_status st = s5d::build_step(items, blob, b->steps[k]);
       if (st != S5D_OK) {

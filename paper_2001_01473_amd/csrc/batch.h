@@ -12,9 +12,11 @@
 
 namespace s5d {
 
-// One round of one grid: bt fused steps of `plan` from src into dst.
+// One round of one grid: bt fused steps of `plan` from src into dst, on
+// resident tiles if `tile` is set.
 struct RoundItem {
   const s5d_plan* plan;
+  const TileKernel2D* tile;
   int bt;
   const void* src;
   void* dst;

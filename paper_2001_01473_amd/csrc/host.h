@@ -12,6 +12,7 @@
 #include "persist2d.h"
 #include "s5d_internal.h"
 #include "stencil5d.h"
+#include "tile.h"
 
 struct s5d_plan {
   s5d_desc d;
@@ -25,6 +26,8 @@ struct s5d_plan {
   bool direct = false;       // direct kernels (one step per launch) instead of blocked ones
   bool chunk_auto = false;   // stream_chunk was chosen by the library (not asked for)
   int64_t slots = 0;         // 2D: resident waves of the plan's variant on the whole device
+  bool tile_ok = false;      // 2D, blocking left to the library: small grids may run on resident tiles
+  int cus = 256;             // compute units of the device
   s5d::Kernel2D by_bt[16];   // 2D: index bt -> kernel for a round of bt steps (same tile)
   s5d::Kernel3D by_bt3[16];  // 3D: likewise
   // device copy of the coefficients in the working type (direct kernels);
@@ -39,24 +42,43 @@ s5d_status fail(s5d_status st, const std::string& msg);
 s5d_status device_fail(hipError_t e, const char* what);
 void clear_error();
 
-// The fused depth of every round of a plan's sweep, in launch order (empty
-// for T = 0).  Round k reads buffer k % 2 and writes buffer (k + 1) % 2; the
+// The rounds of a sweep: the fused depth of each in launch order (empty for T
+// = 0) and, if they run on resident tiles, that kernel (else null: the plan's
+// own kernels).  Round k reads buffer k % 2 and writes buffer (k + 1) % 2; the
 // number of rounds has the parity of T, so the result is in buffer T % 2.
+struct Rounds {
+  std::vector<int> bt;
+  const TileKernel2D* tile = nullptr;
+};
+
+// The rounds of a plan's sweep on its own kernels.
 std::vector<int> plan_rounds(const s5d_plan* p);
+
+// The rounds the library gives a plan that gets about `share` (0 < share <= 1)
+// of the machine: on resident tiles where the plan leaves the choice to the
+// library and the estimate of both says they are faster, else plan_rounds.
+Rounds choose_rounds(const s5d_plan* p, double share);
+
+// The two estimates behind that choice in microseconds: the best rounds on
+// resident tiles (tile null, us = 1e300, if the plan may not run on them) and
+// the plan's own kernels (0 in that case).
+Rounds tile_rounds(const s5d_plan* p, double share, double* us);
+double own_rounds_us(const s5d_plan* p, double share);
 
 // Launch one round of bt fused steps of plan p from src into dst (fields:
 // the per-cell weights of a variable-coefficient plan, else null).
-hipError_t launch_round(const s5d_plan* p, int bt, const void* src, void* dst, hipStream_t stream,
-                        const void* fields = nullptr);
+hipError_t launch_round(const s5d_plan* p, const TileKernel2D* tile, int bt, const void* src, void* dst,
+                        hipStream_t stream, const void* fields = nullptr);
 
 // The batched-launch hooks of the kernel that runs a round of bt steps of p.
 struct BatchHooks {
   LaunchBatchFn launch;  // identifies the kernel variant
   int item_bytes;
 };
-BatchHooks batch_hooks(const s5d_plan* p, int bt);
+BatchHooks batch_hooks(const s5d_plan* p, const TileKernel2D* tile, int bt);
 // Write p's batch item for a round into `item`; returns its workgroups.
-int fill_round_item(const s5d_plan* p, int bt, const void* src, void* dst, void* item, int chunk = 0);
+int fill_round_item(const s5d_plan* p, const TileKernel2D* tile, int bt, const void* src, void* dst, void* item,
+                    int chunk = 0);
 
 // Write the persistent-launch round table entry of one round of p (depth bt,
 // family kernel k) into `out`; returns the round's workgroups (0: too large,

@@ -48,6 +48,7 @@ struct Request {
   s5d_status status = S5D_OK;    // why a FAILED request failed
   double t_arrival = 0, t_admit = -1, t_done = -1;
   std::vector<int> rounds;
+  const s5d::TileKernel2D* tile = nullptr;  // kernel of the rounds, if they run on resident tiles
   size_t next = 0;
   void* buf[2] = {nullptr, nullptr};
   int64_t bytes2 = 0;  // both buffers
@@ -215,7 +216,14 @@ s5d_status admit(s5d_server* s, Request* r) {
   }
   r->init_ev = ev;
   r->init = nullptr;
-  r->rounds = s5d::plan_rounds(&r->plan);
+  // the request's share of the work the server holds
+  double all = 0;
+  for (const Request* q : s->running) all += static_cast<double>(q->updates);
+  for (const Request* q : s->queue) all += static_cast<double>(q->updates);
+  all += static_cast<double>(r->updates);
+  const s5d::Rounds rounds = s5d::choose_rounds(&r->plan, all > 0 ? static_cast<double>(r->updates) / all : 1.0);
+  r->rounds = rounds.bt;
+  r->tile = rounds.tile;
   if (!r->rounds.empty()) {
     e = s5d::launch_boundary_copy(&r->plan, r->buf[0], r->buf[1], s->stream);
     if (e != hipSuccess) return device_fail(e, "boundary copy launch");
@@ -291,11 +299,11 @@ s5d_status check_batchable(const s5d_plan* p) {
   for (int bt : rounds) {
     if (std::find(seen.begin(), seen.end(), bt) != seen.end()) continue;
     seen.push_back(bt);
-    const s5d::BatchHooks h = s5d::batch_hooks(p, bt);
+    const s5d::BatchHooks h = s5d::batch_hooks(p, nullptr, bt);
     if (!h.launch || h.item_bytes <= 0) return fail(S5D_EUNSUPPORTED, "kernel variant without a batched entry point");
     std::vector<unsigned char> item(static_cast<size_t>(h.item_bytes) + 16);
     void* tmp = reinterpret_cast<void*>((reinterpret_cast<uintptr_t>(item.data()) + 15) & ~uintptr_t(15));
-    if (s5d::fill_round_item(p, bt, dummy[0], dummy[1], tmp) <= 0)
+    if (s5d::fill_round_item(p, nullptr, bt, dummy[0], dummy[1], tmp) <= 0)
       return fail(S5D_EUNSUPPORTED, "grid too large for one batched launch");
   }
   return S5D_OK;
@@ -486,8 +494,8 @@ s5d_status s5d_server_tick(s5d_server* s, int32_t* n_running, int32_t* n_queued)
           if (nx[i] >= r->rounds.size()) continue;
           const size_t k = nx[i]++;
           const int bt = r->rounds[k];
-          const int chunk = s5d::shared_chunk(&r->plan, bt, bt * cells_of(r) / step_work);
-          items.push_back(s5d::RoundItem{&r->plan, bt, r->buf[k % 2], r->buf[(k + 1) % 2], chunk});
+          const int chunk = r->tile ? 0 : s5d::shared_chunk(&r->plan, bt, bt * cells_of(r) / step_work);
+          items.push_back(s5d::RoundItem{&r->plan, r->tile, bt, r->buf[k % 2], r->buf[(k + 1) % 2], chunk});
           in_step.back().push_back(i);
           if (nx[i] == r->rounds.size()) fin_after.back().push_back(r);
         }

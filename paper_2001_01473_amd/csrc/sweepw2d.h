@@ -32,6 +32,7 @@
 //    0, and those outputs are replaced by the fixed boundary or discarded).
 #pragma once
 
+#include "gradient.h"
 #include "sweep2d.h"  // EdgeStash, blocks2d and the shared helpers
 
 namespace s5d {
@@ -160,20 +161,7 @@ __device__ __forceinline__ void sweepw2d_body(const SweepW2DArgs& wa, const WinC
           extend(wn[S5D_WSLOT(0)], E);
           constexpr int s_up = S5D_WSLOT(-1), s_dn = S5D_WSLOT(1);
           sfor<CPL>([&](auto K) S5D_INL {
-#pragma clang fp contract(off)
-            const T f = E[R + K];
-            T s2 = cf.c[1];
-            T d = f - wn[s_up][K];
-            s2 = s2 + d * d;
-            d = f - E[R + K - 1];
-            s2 = s2 + d * d;
-            d = f - E[R + K + 1];
-            s2 = s2 + d * d;
-            d = f - wn[s_dn][K];
-            s2 = s2 + d * d;
-            const T root = ieee_sqrt(s2);
-            const T q = T(1) / root;
-            out[K] = cf.c[0] * f + q;
+            out[K] = gradient_cell(cf.c[0], cf.c[1], E[R + K], wn[s_up][K], E[R + K - 1], E[R + K + 1], wn[s_dn][K]);
           });
         } else {
           // the weights of output row o: NP rows of the field (row o - R of
