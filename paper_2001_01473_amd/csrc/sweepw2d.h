@@ -27,9 +27,16 @@
 //    result is the IEEE evaluation of that expression in that order.
 //  OP_VARCOEF: out = sum_k C[k][o] * A[o + o_k] in canonical offset order, one
 //    fused multiply-add per term after the first product; C is n arrays of
-//    the interior's extents (weight k of all cells first), read through
-//    per-row buffer descriptors (rows and columns outside the interior read
-//    0, and those outputs are replaced by the fixed boundary or discarded).
+//    the interior's extents (weight k of all cells first).  Level L reads the
+//    weights of the row L*R behind the newest, so every row of weights is read
+//    BT times; what bounds the sweep is that traffic.  A wave reads each row
+//    once, as whole lane vectors one step ahead, uses it for level 1 and keeps
+//    it in an LDS ring of (BT-1)*R + 1 rows for the other levels.  Every lane
+//    reads back its own columns only: no barrier.  HBM then carries (n + 2) / BT
+//    words per cell and step instead of n + 2 / BT.  Measured at b_T = 4
+//    (GCell/s, weights re-read by every level element by element -> this):
+//    float32 16384^2 5 points 195 -> 634, 9-point star 107 -> 377, 3x3 box
+//    109 -> 420; float64 5 points 144 -> 339.
 #pragma once
 
 #include "gradient.h"
@@ -46,6 +53,21 @@ struct WinCoef {
   T c[OP == OP_GRADIENT ? 2 : 1];
 };
 
+// Per-wave LDS of a window sweep: the EDGE waves' ring of rows, and for
+// per-cell weights the ring of weight rows of levels 2..BT.
+template <typename T, int OP, int R, bool BOX, int BT, int CPL>
+struct alignas(16) WinLds {
+  EdgeStash<T, R, BT, CPL> edge;
+  T wts[OP == OP_VARCOEF && BT > 1 ? (BT - 1) * R + 1 : 1][OP == OP_VARCOEF && BT > 1 ? npts(2, R, BOX) : 1][64][CPL];
+};
+
+// Waves per workgroup: one where a wave's rings take much of the LDS, so that
+// the CU holds as many waves as fit.
+template <int OP>
+constexpr int win_waves() {
+  return OP == OP_VARCOEF ? 1 : kWavesPerBlock;
+}
+
 struct SweepW2DArgs {
   Sweep2DArgs a;
   const void* fields;  // OP_VARCOEF: n_points arrays of I0 x I1 weights
@@ -53,7 +75,8 @@ struct SweepW2DArgs {
 
 template <typename T, int OP, int R, bool BOX, int BT, int CPL, int NR, bool EDGE>
 __device__ __forceinline__ void sweepw2d_body(const SweepW2DArgs& wa, const WinCoef<T, OP>& cf, int lane,
-                                              int tile, int row_a, int row_b, EdgeStash<T, R, BT, CPL>* stash) {
+                                              int tile, int row_a, int row_b,
+                                              WinLds<T, OP, R, BOX, BT, CPL>* lds) {
   constexpr int NWIN = 2 * R + 1;     // rows in a level's window
   constexpr int NS = lcm_i(NWIN, NR); // steps per unrolled iteration
   constexpr int W = 64 * CPL;
@@ -81,13 +104,11 @@ __device__ __forceinline__ void sweepw2d_body(const SweepW2DArgs& wa, const WinC
   bool hcol[CPL];
   if constexpr (EDGE)
     sfor<CPL>([&](auto K) S5D_INL { hcol[K] = colL + K < R || colL + K >= I1 + R; });
-  // weight-field columns: interior column col - R of each row
-  uint32_t foff[CPL];
-  if constexpr (OP == OP_VARCOEF)
-    sfor<CPL>([&](auto K) S5D_INL {
-      const int col = colL + K;
-      foff[K] = (col >= R && col < I1 + R) ? static_cast<uint32_t>(col - R) * WB : kOutOfRange;
-    });
+  // weight columns: interior column colL - R of each row; where the interior
+  // starts inside a lane (wstr: EDGE waves only), the lane reads the row's first
+  // cells and moves them up by R
+  const bool wstr = EDGE && colL < R && colL + CPL > R;
+  const uint32_t foff = wstr ? 0u : static_cast<uint32_t>(colL - R) * WB;
 
   const T* __restrict__ src = static_cast<const T*>(a.src);
   T* __restrict__ dst = static_cast<T*>(a.dst);
@@ -127,6 +148,22 @@ __device__ __forceinline__ void sweepw2d_body(const SweepW2DArgs& wa, const WinC
     __builtin_amdgcn_sched_barrier(0);
   });
 
+  // the weights of grid row o (NP rows of the field; out of range: 0), one
+  // step ahead of level 1
+  constexpr int DW = (BT - 1) * R + 1;  // rows in the LDS ring of weights
+  RowV wnext[OP == OP_VARCOEF ? NP : 1];
+  auto load_weights = [&](int o) S5D_INL {
+    const bool orow = o >= R && o < I0 + R;
+    sfor<NP>([&](auto KI) S5D_INL {
+      const auto rs = make_rsrc(fld + (static_cast<int64_t>(KI) * I0 + (orow ? o - R : 0)) * I1,
+                                orow ? static_cast<uint32_t>(I1) * WB : 0u);
+      T t[CPL];
+      buf_load_lane(t, rs, foff);
+      sfor<CPL>([&](auto K) S5D_INL { wnext[KI][+K] = t[K]; });
+    });
+  };
+  if constexpr (OP == OP_VARCOEF) load_weights(s0 - R);
+
   // one output cell of a level from its window; o is the output row
   auto extend = [&](const T (&row)[CPL], T (&E)[XL]) S5D_INL {
     sfor<CPL>([&](auto K) S5D_INL { E[R + K] = row[K]; });
@@ -137,12 +174,13 @@ __device__ __forceinline__ void sweepw2d_body(const SweepW2DArgs& wa, const WinC
   };
 
   int srow = s0 % MROW;  // ring slot of row s, stepped along with s
+  int swt = 0;           // slot of the weights level 1 uses at this step
   auto iteration = [&](const int sb) S5D_INL {
     sfor<NS>([&](auto PH) S5D_INL {
       const int s = sb + PH;
       load_vec(ringv[pmod(PH - 1, NR)], s + NR - 1);
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (EDGE) sfor<CPL>([&](auto K) S5D_INL { stash->rows[srow][lane][K] = ringv[PH % NR][+K]; });
+      if constexpr (EDGE) sfor<CPL>([&](auto K) S5D_INL { lds->edge.rows[srow][lane][K] = ringv[PH % NR][+K]; });
       T cur[CPL];
       sfor<CPL>([&](auto K) S5D_INL { cur[K] = ringv[PH % NR][+K]; });
 
@@ -164,15 +202,28 @@ __device__ __forceinline__ void sweepw2d_body(const SweepW2DArgs& wa, const WinC
             out[K] = gradient_cell(cf.c[0], cf.c[1], E[R + K], wn[s_up][K], E[R + K - 1], E[R + K + 1], wn[s_dn][K]);
           });
         } else {
-          // the weights of output row o: NP rows of the field (row o - R of
-          // the interior), every lane loading its CPL columns
-          const bool orow = o >= R && o < I0 + R;
           T wgt[NP][CPL];
-          sfor<NP>([&](auto KI) S5D_INL {
-            const auto rs = make_rsrc(fld + (static_cast<int64_t>(KI) * I0 + (orow ? o - R : 0)) * I1,
-                                      orow ? static_cast<uint32_t>(I1) * WB : 0u);
-            sfor<CPL>([&](auto K) S5D_INL { buf_load(wgt[KI][K], rs, foff[K]); });
-          });
+          if constexpr (lv == 1) {
+            sfor<NP>([&](auto KI) S5D_INL {
+              sfor<CPL>([&](auto K) S5D_INL {
+                wgt[KI][K] = wnext[KI][+K];
+                if constexpr (EDGE) {
+                  if constexpr (K >= R) wgt[KI][K] = wstr ? wnext[KI][K - R] : wgt[KI][K];
+                }
+              });
+            });
+            if constexpr (BT > 1)
+              sfor<NP>([&](auto KI) S5D_INL {
+                sfor<CPL>([&](auto K) S5D_INL { lds->wts[swt][KI][lane][K] = wgt[KI][K]; });
+              });
+          } else {
+            constexpr int back = (lv - 1) * R;
+            const int ws = swt < back ? swt - back + DW : swt - back;
+            sfor<NP>([&](auto KI) S5D_INL {
+              const LaneVec<T, CPL> v = *reinterpret_cast<const LaneVec<T, CPL>*>(lds->wts[ws][KI][lane]);
+              sfor<CPL>([&](auto K) S5D_INL { wgt[KI][K] = v.v[K]; });
+            });
+          }
           T E[2 * R + 1][XL];
           sfor<2 * R + 1>([&](auto D) S5D_INL {
             if constexpr (BOX || D == R) extend(wn[S5D_WSLOT(D - R)], E[D]);
@@ -196,13 +247,18 @@ __device__ __forceinline__ void sweepw2d_body(const SweepW2DArgs& wa, const WinC
             });
             out[K] = acc;
           });
+          if constexpr (lv == 1) {
+            __builtin_amdgcn_sched_barrier(0);
+            load_weights(s + 1 - R);
+            __builtin_amdgcn_sched_barrier(0);
+          }
         }
 #undef S5D_WSLOT
 
         if constexpr (EDGE && lv < BT) {
           const int os = srow - lv * R;  // ring slot of row o
           const bool rowb = o < R || o >= I0 + R;
-          const LaneVec<T, CPL> hv = *reinterpret_cast<const LaneVec<T, CPL>*>(stash->rows[os < 0 ? os + MROW : os][lane]);
+          const LaneVec<T, CPL> hv = *reinterpret_cast<const LaneVec<T, CPL>*>(lds->edge.rows[os < 0 ? os + MROW : os][lane]);
           sfor<CPL>([&](auto K) S5D_INL { out[K] = (rowb || hcol[K]) ? hv.v[K] : out[K]; });
         }
 
@@ -217,6 +273,7 @@ __device__ __forceinline__ void sweepw2d_body(const SweepW2DArgs& wa, const WinC
         }
       });
       if constexpr (EDGE) srow = srow + 1 == MROW ? 0 : srow + 1;
+      if constexpr (OP == OP_VARCOEF) swt = swt + 1 == DW ? 0 : swt + 1;
     });
   };
   iteration(s0);
@@ -224,8 +281,8 @@ __device__ __forceinline__ void sweepw2d_body(const SweepW2DArgs& wa, const WinC
 }
 
 template <typename T, int OP, int R, bool BOX, int BT, int CPL, int NR>
-__global__ __launch_bounds__(64 * kWavesPerBlock) void sweepw2d_kernel(SweepW2DArgs wa, WinCoef<T, OP> cf) {
-  __shared__ EdgeStash<T, R, BT, CPL> stash[kWavesPerBlock];
+__global__ __launch_bounds__(64 * win_waves<OP>()) void sweepw2d_kernel(SweepW2DArgs wa, WinCoef<T, OP> cf) {
+  __shared__ WinLds<T, OP, R, BOX, BT, CPL> lds[win_waves<OP>()];
   constexpr int W = 64 * CPL;
   constexpr int LO = overlap_left(BT, R, sizeof(T));
   constexpr int C = compute_width(W, BT, R, sizeof(T));
@@ -236,7 +293,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void sweepw2d_kernel(SweepW2DA
   const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nb = a.g.nb;
   const int x = lb % nb;
-  const int wid = (lb / nb) * kWavesPerBlock + wib;
+  const int wid = (lb / nb) * win_waves<OP>() + wib;
   if (wid >= a.nwaves) return;
   const int lane = threadIdx.x & 63;
   const int tile = wid % a.ntiles;
@@ -245,11 +302,13 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void sweepw2d_kernel(SweepW2DA
   if (row_b <= row_a) return;
   const int P1 = a.I1 + 2 * R;
   const int col0 = R + tile * C - LO;
-  const bool edge = col0 < 0 || col0 + W > P1 || row_a - (BT - 1) * R < R || row_b + (BT - 1) * R > a.I0 + R;
+  // (the weights' first columns start inside a lane of a tile at col0 < R)
+  const bool edge = col0 < (OP == OP_VARCOEF ? R : 0) || col0 + W > P1 || row_a - (BT - 1) * R < R ||
+                    row_b + (BT - 1) * R > a.I0 + R;
   if (edge)
-    sweepw2d_body<T, OP, R, BOX, BT, CPL, NR, true>(wa, cf, lane, tile, row_a, row_b, &stash[wib]);
+    sweepw2d_body<T, OP, R, BOX, BT, CPL, NR, true>(wa, cf, lane, tile, row_a, row_b, &lds[wib]);
   else
-    sweepw2d_body<T, OP, R, BOX, BT, CPL, NR, false>(wa, cf, lane, tile, row_a, row_b, &stash[wib]);
+    sweepw2d_body<T, OP, R, BOX, BT, CPL, NR, false>(wa, cf, lane, tile, row_a, row_b, &lds[wib]);
 }
 
 template <typename T, int OP, int R, bool BOX, int BT, int CPL, int NR>
@@ -275,19 +334,21 @@ hipError_t launch_sweepw2d(const Round2D& rd) {
   } else {
     cf.c[0] = T(0);
   }
-  const int nblk = blocks2d(a);
-  hipLaunchKernelGGL((sweepw2d_kernel<T, OP, R, BOX, BT, CPL, NR>), dim3(nblk), dim3(64 * kWavesPerBlock), 0,
+  const int nblk = a.g.nb * ((a.nwaves + win_waves<OP>() - 1) / win_waves<OP>());
+  hipLaunchKernelGGL((sweepw2d_kernel<T, OP, R, BOX, BT, CPL, NR>), dim3(nblk), dim3(64 * win_waves<OP>()), 0,
                      rd.stream, wa, cf);
   return hipGetLastError();
 }
 
+// Resident workgroups of kWavesPerBlock waves, the unit of the stream-block
+// chooser, rounded up.
 template <typename T, int OP, int R, bool BOX, int BT, int CPL, int NR>
 int occupancy_sweepw2d() {
   int nb = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, sweepw2d_kernel<T, OP, R, BOX, BT, CPL, NR>,
-                                                   64 * kWavesPerBlock, 0) != hipSuccess)
+                                                   64 * win_waves<OP>(), 0) != hipSuccess)
     return 0;
-  return nb;
+  return (nb * win_waves<OP>() + kWavesPerBlock - 1) / kWavesPerBlock;
 }
 
 // Window kernels have no batched entry point: batches and servers reject
