@@ -85,7 +85,7 @@ Default3D default_tuning3(int kind, int box, int r, int expr = 0) {
     if (r == 1) return box ? Default3D{2, 4} : Default3D{3, 2};
     return box ? Default3D{1, 2} : Default3D{2, 2};
   }
-  if (r == 1) return box ? Default3D{2, 4, 64} : Default3D{3, 2};
+  if (r == 1) return box ? Default3D{2, 4, 64} : Default3D{3, 4};
   return box ? Default3D{1, 4} : Default3D{2, 4};
 }
 int default_bt3(int kind, int box, int r, int expr) { return default_tuning3(kind, box, r, expr).bt; }

@@ -15,7 +15,7 @@
 //    shifts (as in the 2D kernel); axis-1 neighbours that live in another
 //    wave come from a double-buffered LDS exchange of the R edge rows of each
 //    wave: one barrier per level and step, as the paper's double-buffered
-//    shared memory;
+//    shared memory, or (star stencils) one per step;
 //  * partial sums along axis 0: an arriving plane is pushed into the 2R+1
 //    output planes it feeds, so a level holds 2R accumulator planes; each
 //    output is summed in canonical (d0, d1, d2) order;
@@ -30,10 +30,21 @@
 
 namespace s5d {
 
+// LDS exchange of the waves' first and last R rows, double-buffered.  Star
+// stencils exchange the rows of every level of a step at once (ONCE) while the
+// buffers of two workgroups fit a CU; the others, and boxes, level by level.
+// (With one buffer and a second barrier for the stars that do not fit, the
+// float64 13-point star at 512^3 fell from 299 to 268 GCell/s.)
+template <typename T, int R, bool BOX, int BT, int CPL, int NW>
+struct Exchange3D {
+  static constexpr bool ONCE = !BOX && 2 * BT * NW * 2 * R * 64 * CPL * static_cast<int>(sizeof(T)) <= 80 * 1024;
+  T rows[2][ONCE ? BT : 1][NW][2 * R][64 * CPL];
+};
+
 template <typename T, int ACC, int EXPR, int R, bool BOX, int BT, int CPL, int M, int NW, int NR, bool EDGE>
 __device__ __forceinline__ void sweep3d_body(const Sweep3DArgs& a, const CoefPack<T, ncoef(3, R, BOX, EXPR)>& cf,
                                              int w, int lane, int t1, int t2, int chunk,
-                                             T (*xbuf)[NW][2 * R][64 * CPL]) {
+                                             Exchange3D<T, R, BOX, BT, CPL, NW>& xch) {
   static_assert(R <= M, "an edge-row exchange reaches one neighbouring wave only");
   constexpr int NA = 2 * R;          // pending output planes per level
   constexpr int NS = lcm_i(NA, NR);  // steps per unrolled iteration
@@ -138,6 +149,130 @@ __device__ __forceinline__ void sweep3d_body(const Sweep3DArgs& a, const CoefPac
     __builtin_amdgcn_sched_barrier(0);
   });
 
+  // the compute region of plane o of the last level (dropped outside the block)
+  auto store_plane = [&](const T (&out)[M][CPL], const int o) S5D_INL {
+    const bool keep_pl = o >= pl_a && o < pl_b;
+    sfor<M>([&](auto MI) S5D_INL {
+      const bool keep = keep_pl && row_st[MI];
+      const auto rs = make_rsrc(row_ptr(dst, keep ? o : pl_a, keep ? row0 + MI : r_first),
+                                keep ? st_bytes : 0u);
+      buf_store_cells<0>(out[MI], rs, vstore);
+      if constexpr (LK != 0) buf_store_cells<LK>(out[MI], rs, lstore);
+    });
+  };
+
+  // Star stencils.  An arriving plane completes output plane p-R with a term of
+  // its own cell, so all the levels' arriving planes of a step are known before
+  // any neighbour is: emit them level by level, publish the edge rows of all of
+  // them, meet once, then push each into the planes it feeds.  A level's freed
+  // accumulator slot is empty in between, so holding the planes over the
+  // barrier takes no registers.  One barrier and one LDS round trip a step
+  // instead of one per level: float32 7-point star at 512^3 (b_T = 3) 1128 ->
+  // 1227 GCell/s, 256^3 786 -> 891; 13-point star (b_T = 2) 585 -> 656.
+  const int wu = w > 0 ? w - 1 : w, wd = w + 1 < NW ? w + 1 : w;
+  auto star_iteration = [&](const int sb) S5D_INL {
+    sfor<NS>([&](auto PH) S5D_INL {
+      const int s = sb + PH;
+      load_plane(ring[pmod(PH - 1, NR)], s + NR - 1);
+      __builtin_amdgcn_sched_barrier(0);
+      constexpr int par = PH & 1;  // exchange buffer (NS is even)
+      T lev[BT][M][CPL];  // the plane arriving at each level
+      sfor<M>([&](auto MI) S5D_INL { sfor<CPL>([&](auto K) S5D_INL { lev[0][MI][K] = ring[PH % NR][MI][+K]; }); });
+      sfor<BT>([&](auto LI) S5D_INL {
+        constexpr int lv = LI + 1;
+        constexpr int so = pmod(PH - LI * R + R, NA);  // slot of planes p-R and p+R
+        constexpr int cs = PH % R;                     // delay-line slot of planes p and p-R
+        sfor<R>([&](auto J) S5D_INL {
+          sfor<CPL>([&](auto K) S5D_INL {
+            xch.rows[par][LI][w][J][lane * CPL + K] = lev[LI][J][K];
+            xch.rows[par][LI][w][R + J][lane * CPL + K] = lev[LI][M - R + J][K];
+          });
+        });
+        T out[M][CPL];
+        sfor<M>([&](auto MI) S5D_INL {
+          sfor<CPL>([&](auto K) S5D_INL {
+            Accum<T, ACC> v = acc[LI][so][MI][K];
+            v.add(cf.c[6 * R], lev[LI][MI][K]);
+            out[MI][K] = finish<EXPR>(v.value(), cf);
+          });
+        });
+        if constexpr (EDGE && lv < BT) {
+          // boundary cells take the value plane o had when it arrived here (R
+          // steps ago); then the slot records plane p
+          const int o = s - lv * R;
+          const bool pl_hal = o < R || o >= I0 + R;
+          sfor<M>([&](auto MI) S5D_INL {
+            const bool rh = pl_hal || row_hal[MI];
+            sfor<CPL>([&](auto K) S5D_INL {
+              out[MI][K] = (rh || hcol[K]) ? cen[LI][cs][MI][K] : out[MI][K];
+              cen[LI][cs][MI][K] = lev[LI][MI][K];
+            });
+          });
+        }
+        if constexpr (lv < BT)
+          sfor<M>([&](auto MI) S5D_INL { sfor<CPL>([&](auto K) S5D_INL { lev[lv < BT ? lv : 0][MI][K] = out[MI][K]; }); });
+        else
+          store_plane(out, s - BT * R);
+      });
+      __syncthreads();
+      sfor<BT>([&](auto LI) S5D_INL {
+        constexpr int pm = pmod(PH - LI * R, NA);  // p mod 2R
+        Accum<T, ACC>(&A)[NA][M][CPL] = acc[LI];
+        T(&cur)[M][CPL] = lev[LI];
+        T X1[M + 2 * R][CPL];  // the rows with R more above and below
+        sfor<R>([&](auto J) S5D_INL {
+          const LaneVec<T, CPL> up =
+              *reinterpret_cast<const LaneVec<T, CPL>*>(&xch.rows[par][LI][wu][R + J][lane * CPL]);
+          const LaneVec<T, CPL> dn =
+              *reinterpret_cast<const LaneVec<T, CPL>*>(&xch.rows[par][LI][wd][J][lane * CPL]);
+          sfor<CPL>([&](auto K) S5D_INL {
+            X1[J][K] = up.v[K];
+            X1[R + M + J][K] = dn.v[K];
+          });
+        });
+        sfor<M>([&](auto MI) S5D_INL { sfor<CPL>([&](auto K) S5D_INL { X1[R + MI][K] = cur[MI][K]; }); });
+        // output p+R starts: (-R, 0, 0); then p+R-1 .. p-R+1
+        sfor<M>([&](auto MI) S5D_INL {
+          sfor<CPL>([&](auto K) S5D_INL { A[pmod(pm + R, NA)][MI][K].first(cf.c[0], cur[MI][K]); });
+        });
+        sfor<2 * R - 1>([&](auto J) S5D_INL {
+          constexpr int d0 = -R + 1 + J;
+          constexpr int sl = pmod(pm - d0, NA);
+          sfor<M>([&](auto MI) S5D_INL {
+            if constexpr (d0 != 0) {
+              constexpr int ci = d0 < 0 ? d0 + R : 5 * R + d0;
+              sfor<CPL>([&](auto K) S5D_INL { A[sl][MI][K].add(cf.c[ci], cur[MI][K]); });
+            } else {
+              // centre plane: (0,d1,0) d1<0, then (0,0,d2), then (0,d1,0) d1>0
+              T E[XL];
+              sfor<CPL>([&](auto K) S5D_INL { E[R + K] = cur[MI][K]; });
+              if constexpr (!FOLD)
+                sfor<R>([&](auto Q) S5D_INL {
+                  E[Q] = lane_from_lower(cur[MI][CPL - R + Q]);
+                  E[R + CPL + Q] = lane_from_upper(cur[MI][Q]);
+                });
+              sfor<CPL>([&](auto K) S5D_INL {
+                Accum<T, ACC>& ak = A[sl][MI][K];
+                sfor<R>([&](auto Q) S5D_INL { ak.add(cf.c[R + Q], X1[MI + Q][K]); });
+                sfor<2 * R + 1>([&](auto D2) S5D_INL {
+                  constexpr int e = decltype(K)::value + decltype(D2)::value;  // extended column
+                  if constexpr (FOLD && (e < R || e >= R + CPL)) {
+                    constexpr bool shr = e < R;  // from lane l-1, else lane l+1
+                    constexpr int sc = shr ? CPL - R + e : e - R - CPL;
+                    ak.s = fma_dpp<shr>(ak.s, cur[MI][sc], cv[D2]);
+                  } else {
+                    ak.add(cf.c[2 * R + D2], E[e]);
+                  }
+                });
+                sfor<R>([&](auto Q) S5D_INL { ak.add(cf.c[4 * R + 1 + Q], X1[MI + R + 1 + Q][K]); });
+              });
+            }
+          });
+        });
+      });
+    });
+  };
+
   auto iteration = [&](const int sb) S5D_INL {
     sfor<NS>([&](auto PH) S5D_INL {
       const int s = sb + PH;
@@ -159,16 +294,15 @@ __device__ __forceinline__ void sweep3d_body(const Sweep3DArgs& a, const CoefPac
         // those rows lie in the overlap that the valid region discards)
         sfor<R>([&](auto J) S5D_INL {
           sfor<CPL>([&](auto K) S5D_INL {
-            xbuf[par][w][J][lane * CPL + K] = cur[J][K];
-            xbuf[par][w][R + J][lane * CPL + K] = cur[M - R + J][K];
+            xch.rows[par][0][w][J][lane * CPL + K] = cur[J][K];
+            xch.rows[par][0][w][R + J][lane * CPL + K] = cur[M - R + J][K];
           });
         });
         __syncthreads();
-        const int wu = w > 0 ? w - 1 : w, wd = w + 1 < NW ? w + 1 : w;
         T X[XR][XL];  // extended plane around this wave's rows
         sfor<R>([&](auto J) S5D_INL {
-          const LaneVec<T, CPL> up = *reinterpret_cast<const LaneVec<T, CPL>*>(&xbuf[par][wu][R + J][lane * CPL]);
-          const LaneVec<T, CPL> dn = *reinterpret_cast<const LaneVec<T, CPL>*>(&xbuf[par][wd][J][lane * CPL]);
+          const LaneVec<T, CPL> up = *reinterpret_cast<const LaneVec<T, CPL>*>(&xch.rows[par][0][wu][R + J][lane * CPL]);
+          const LaneVec<T, CPL> dn = *reinterpret_cast<const LaneVec<T, CPL>*>(&xch.rows[par][0][wd][J][lane * CPL]);
           sfor<CPL>([&](auto K) S5D_INL {
             X[J][R + K] = up.v[K];
             X[R + M + J][R + K] = dn.v[K];
@@ -265,27 +399,24 @@ __device__ __forceinline__ void sweep3d_body(const Sweep3DArgs& a, const CoefPac
         if constexpr (lv < BT) {
           sfor<M>([&](auto MI) S5D_INL { sfor<CPL>([&](auto K) S5D_INL { cur[MI][K] = out[MI][K]; }); });
         } else {
-          const int o = s - BT * R;
-          const bool keep_pl = o >= pl_a && o < pl_b;
-          sfor<M>([&](auto MI) S5D_INL {
-            const bool keep = keep_pl && row_st[MI];
-            const auto rs = make_rsrc(row_ptr(dst, keep ? o : pl_a, keep ? row0 + MI : r_first),
-                                      keep ? st_bytes : 0u);
-            buf_store_cells<0>(out[MI], rs, vstore);
-            if constexpr (LK != 0) buf_store_cells<LK>(out[MI], rs, lstore);
-          });
+          store_plane(out, s - BT * R);
         }
       });
     });
   };
-  iteration(s0);
-  for (int it = 1; it < niter; ++it) iteration(s0 + it * NS);
+  if constexpr (Exchange3D<T, R, BOX, BT, CPL, NW>::ONCE) {
+    star_iteration(s0);
+    for (int it = 1; it < niter; ++it) star_iteration(s0 + it * NS);
+  } else {
+    iteration(s0);
+    for (int it = 1; it < niter; ++it) iteration(s0 + it * NS);
+  }
 }
 
 // Workgroup lb of one grid's launch: one (tile, stream block) pair.
 template <typename T, int ACC, int EXPR, int R, bool BOX, int BT, int CPL, int M, int NW, int NR>
 __device__ __forceinline__ void sweep3d_block(const Sweep3DArgs& a, const CoefPack<T, ncoef(3, R, BOX, EXPR)>& cf, int lb,
-                                              T (&xbuf)[2][NW][2 * R][64 * CPL]) {
+                                              Exchange3D<T, R, BOX, BT, CPL, NW>& xch) {
   constexpr int B1 = NW * M, B2 = 64 * CPL;
   constexpr int C1 = B1 - 2 * BT * R, C2 = compute_width(B2, BT, R, sizeof(T));
   static_assert(R <= CPL, "the lane exchange reaches one neighbouring lane only");
@@ -303,15 +434,15 @@ __device__ __forceinline__ void sweep3d_block(const Sweep3DArgs& a, const CoefPa
   const bool edge = row0 < 0 || row0 + B1 > P1 || col0 < 0 || col0 + B2 > P2 ||
                     pl_a - (BT - 1) * R < R || pl_b + (BT - 1) * R > a.I0 + R;
   if (edge)
-    sweep3d_body<T, ACC, EXPR, R, BOX, BT, CPL, M, NW, NR, true>(a, cf, w, lane, t1, t2, chunk, xbuf);
+    sweep3d_body<T, ACC, EXPR, R, BOX, BT, CPL, M, NW, NR, true>(a, cf, w, lane, t1, t2, chunk, xch);
   else
-    sweep3d_body<T, ACC, EXPR, R, BOX, BT, CPL, M, NW, NR, false>(a, cf, w, lane, t1, t2, chunk, xbuf);
+    sweep3d_body<T, ACC, EXPR, R, BOX, BT, CPL, M, NW, NR, false>(a, cf, w, lane, t1, t2, chunk, xch);
 }
 
 template <typename T, int ACC, int EXPR, int R, bool BOX, int BT, int CPL, int M, int NW, int NR>
 __global__ __launch_bounds__(64 * NW) void sweep3d_kernel(Sweep3DArgs a, CoefPack<T, ncoef(3, R, BOX, EXPR)> cf) {
-  __shared__ T xbuf[2][NW][2 * R][64 * CPL];
-  sweep3d_block<T, ACC, EXPR, R, BOX, BT, CPL, M, NW, NR>(a, cf, xcd_logical_block(blockIdx.x, gridDim.x), xbuf);
+  __shared__ Exchange3D<T, R, BOX, BT, CPL, NW> xch;
+  sweep3d_block<T, ACC, EXPR, R, BOX, BT, CPL, M, NW, NR>(a, cf, xcd_logical_block(blockIdx.x, gridDim.x), xch);
 }
 
 // One grid of a batched launch: its geometry and coefficients.
@@ -325,12 +456,12 @@ struct alignas(16) Item3D {
 template <typename T, int ACC, int EXPR, int R, bool BOX, int BT, int CPL, int M, int NW, int NR>
 __global__ __launch_bounds__(64 * NW) void sweep3d_batch_kernel(const Item3D<T, ncoef(3, R, BOX, EXPR)>* __restrict__ items,
                                                               const BlockMap* __restrict__ map) {
-  __shared__ T xbuf[2][NW][2 * R][64 * CPL];
+  __shared__ Exchange3D<T, R, BOX, BT, CPL, NW> xch;
   const BlockMap m = map[xcd_logical_block(blockIdx.x, gridDim.x)];
   const Item3D<T, ncoef(3, R, BOX, EXPR)>& it = items[__builtin_amdgcn_readfirstlane(m.item)];
   const Sweep3DArgs a = it.a;
   const CoefPack<T, ncoef(3, R, BOX, EXPR)> cf = it.cf;
-  sweep3d_block<T, ACC, EXPR, R, BOX, BT, CPL, M, NW, NR>(a, cf, __builtin_amdgcn_readfirstlane(m.block), xbuf);
+  sweep3d_block<T, ACC, EXPR, R, BOX, BT, CPL, M, NW, NR>(a, cf, __builtin_amdgcn_readfirstlane(m.block), xch);
 }
 
 // Geometry of one grid's launch; returns its workgroup count (0 if it does
