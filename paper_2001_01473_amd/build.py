@@ -41,11 +41,12 @@ DEVICE_FLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC",
                 "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                 "-I" + CSRC, "-I" + INCLUDE]
 
-HOST_SOURCES = ["abi.cpp", "batch.cpp", "server.cpp", "tune.cpp", "halo.hip", "norms.hip", "direct.hip", "tile2d.hip"]
+HOST_SOURCES = ["abi.cpp", "batch.cpp", "server.cpp", "tune.cpp", "halo.hip", "norms.hip", "direct.hip", "tile2d.hip",
+                "march3d.hip"]
 HEADERS = ["s5d_internal.h", "kcommon.h", "sweep2d.h", "sweep3d.h", "sweepw2d.h", "sweepp2d.h", "persist2d.h",
            "persist_schedule.h"]
 HOST_HEADERS = ["host.h", "batch.h", "norms.h", "direct.h", "stream2d.h", "stream3d.h", "tile.h", "tile2d.h",
-                "gradient.h"]  # not included by the variant units
+                "gradient.h", "march.h", "march3d.h"]  # not included by the variant units
 
 # Kernel kinds: (name, C++ type, 32-bit words per element, accumulation
 # policy).  Kind 2 is float32 with compensated (Dot2) accumulation.

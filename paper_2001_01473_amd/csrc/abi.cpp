@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "host.h"
+#include "march.h"
 #include "norms.h"
 
 using s5d::Entry2D;
@@ -276,7 +277,17 @@ s5d_status plan_direct(s5d_plan* p, const s5d_tuning& req, int box, int r) {
     if (!p->by_bt[1].launch) return fail(S5D_EUNSUPPORTED, "no direct 2D kernel for this stencil");
     p->tun.tile0 = p->by_bt[1].tile;
   } else {
-    p->by_bt3[1] = s5d::direct_kernel3d(p->kind, r, box != 0);
+    // plain stars of radius 2..4 march once the grid has enough tiles to fill
+    // the machine (64^3, float32 radius 4: row streaming 20 us a step, marching
+    // 30; 143 x 151 x 140: 66 and 24) and its planes stay within a buffer
+    // descriptor's range; the float32 radius-2 star keeps row streaming where
+    // its rows are whole waves (512^3: 315 and 335, 420 x 512 x 483: 358 and 184)
+    const double cells = static_cast<double>(p->d.interior[0]) * static_cast<double>(p->d.interior[1]) *
+                         static_cast<double>(p->d.interior[2]);
+    const double plane = static_cast<double>(p->padded[1]) * static_cast<double>(p->padded[2]) * p->elem;
+    const bool whole_rows = p->kind == KIND_F32 && r == 2 && p->d.interior[2] % 256 == 0;
+    if (!box && cells >= 1 << 20 && plane < 2147483648.0 && !whole_rows) p->by_bt3[1] = s5d::march_kernel3d(p->kind, r);
+    if (!p->by_bt3[1].launch) p->by_bt3[1] = s5d::direct_kernel3d(p->kind, r, box != 0);
     if (!p->by_bt3[1].launch) return fail(S5D_EUNSUPPORTED, "no direct 3D kernel for this stencil");
     p->tun.tile0 = p->by_bt3[1].m;
   }
