@@ -158,8 +158,10 @@ Default2D default_tuning(int kind, int box, int r, int expr = 0) {
   if (expr == s5d::EXPR_VARCOEF) return {4, kind == KIND_F64 ? 2 : 4};
   if (expr == s5d::EXPR_DIV) {
     const int c = kind == KIND_F64 ? 2 : 4;
+    // 5 points at 8000^2, 60 steps, b_T = 4 / 6 / 8: float32 2270 / 2020 / 2047 us,
+    // float64 3811 / 3070 / 3032; the shallower pair leaves smaller grids more blocks
     if (box) return {kind == KIND_F64 ? 6 : 5, c};
-    return {r == 1 ? 8 : 5, c};
+    return {r == 1 ? 6 : 5, c};
   }
   static const Default2D f32_star[4] = {{10, 4}, {7, 4}, {5, 4}, {3, 4}};
   static const Default2D f32_box[4] = {{7, 4}, {3, 4}, {2, 4}, {1, 4}};
@@ -495,7 +497,7 @@ double own_us(const s5d_plan* p, double share) {
   const double T = static_cast<double>(p->d.steps);
   const double terms = p->expr == EXPR_GRADIENT ? 38 : npts(2, r, p->d.shape == S5D_BOX) *
                                                                (p->kind == KIND_F32_COMP ? 8.0 : 1.0) +
-                                                           (p->expr == EXPR_DIV ? 8 : 0);
+                                                           (p->expr == EXPR_DIV ? 5 : 0);
   // one step per launch (the compensated stencils but the 5-point star)
   if (p->direct) return T * (kRoundUs + 2.5 + cells * terms / 64 / (p->cus * share) / kClocksPerUs);
   const int cpl = p->tun.cells_per_lane;

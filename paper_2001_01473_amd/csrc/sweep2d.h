@@ -129,6 +129,7 @@ __device__ __forceinline__ void sweep2d_body(const Sweep2DArgs& a, const CoefPac
       if constexpr (folded_coef2d<R, BOX>(I)) cv[I] = to_vgpr(cf.c[I]);
     });
 
+  const Finish<EXPR, T, CoefPack<T, ncoef(2, R, BOX, EXPR)>> fin(cf);
   Accum<T, ACC> acc[BT][NA][CPL];
   using RowV = T __attribute__((ext_vector_type(CPL)));
   RowV ringv[NR];
@@ -214,8 +215,9 @@ __device__ __forceinline__ void sweep2d_body(const Sweep2DArgs& a, const CoefPac
         sfor<CPL>([&](auto K) S5D_INL {
           Accum<T, ACC> v = A[so][K];
           add_row(ic<R>{}, v, K, std::false_type{});
-          out[K] = finish<EXPR>(v.value(), cf);
+          out[K] = v.value();
         });
+        fin(out);
         // 2. output p+R starts in the freed slot (d0 = -R)
         sfor<CPL>([&](auto K) S5D_INL { add_row(ic<-R>{}, A[so][K], K, std::true_type{}); });
         // 3. outputs p+R-1 .. p-R+1 (d0 = -R+1 .. R-1)

@@ -126,6 +126,11 @@ __device__ __forceinline__ void sweep3d_body(const Sweep3DArgs& a, const CoefPac
   // Only levels below BT pass values on: the last level is stored, and the
   // boundary is never stored, so it needs no pass-through.
   constexpr int NCEN = BT > 1 ? BT - 1 : 1;
+  const Finish<EXPR, T, CoefPack<T, ncoef(3, R, BOX, EXPR)>> fin(cf);
+  // float64 divides cell by cell: the quotients of a tile row's cells together
+  // take more registers than there are (27-point box, b_T = 3: 229 VGPRs, 256
+  // and a spill)
+  constexpr bool CELLWISE = EXPR == EXPR_DIV && sizeof(T) == 8;
   Accum<T, ACC> acc[BT][NA][M][CPL];
   T cen[NCEN][R][M][CPL];  // last R arriving planes of levels 1..BT-1 (boundary pass-through)
   RowV ring[NR][M];
@@ -193,9 +198,11 @@ __device__ __forceinline__ void sweep3d_body(const Sweep3DArgs& a, const CoefPac
           sfor<CPL>([&](auto K) S5D_INL {
             Accum<T, ACC> v = acc[LI][so][MI][K];
             v.add(cf.c[6 * R], lev[LI][MI][K]);
-            out[MI][K] = finish<EXPR>(v.value(), cf);
+            out[MI][K] = v.value();
+            if constexpr (CELLWISE) out[MI][K] /= fin.c0;
           });
         });
+        if constexpr (!CELLWISE) fin(out);
         if constexpr (EDGE && lv < BT) {
           // boundary cells take the value plane o had when it arrived here (R
           // steps ago); then the slot records plane p
@@ -368,9 +375,11 @@ __device__ __forceinline__ void sweep3d_body(const Sweep3DArgs& a, const CoefPac
           sfor<CPL>([&](auto K) S5D_INL {
             Accum<T, ACC> v = A[so][MI][K];
             add_plane(ic<R>{}, v, MI, K, std::false_type{});
-            out[MI][K] = finish<EXPR>(v.value(), cf);
+            out[MI][K] = v.value();
+            if constexpr (CELLWISE) out[MI][K] /= fin.c0;
           });
         });
+        if constexpr (!CELLWISE) fin(out);
         sfor<M>([&](auto MI) S5D_INL {
           sfor<CPL>([&](auto K) S5D_INL { add_plane(ic<-R>{}, A[so][MI][K], MI, K, std::true_type{}); });
         });

@@ -79,6 +79,17 @@ __device__ __forceinline__ void tile2d_body(const Tile2DArgs& a, const CoefPack<
   const bool grid_rows = row0 + M > R && row0 < I0 + R;  // does this wave hold interior rows?
   const int wu = w > 0 ? w - 1 : w, wd = w + 1 < NW ? w + 1 : w;
 
+  const Finish<EXPR, T, CoefPack<T, ncoef(2, R, BOX, EXPR)>> fin(cf);
+  // row MI takes its new values, except the cells that keep theirs
+  auto keep = [&](auto MI, const T (&out)[CPL]) S5D_INL {
+    if constexpr (EDGE) {
+      const bool rowb = row0 + MI < R || row0 + MI >= I0 + R;
+      sfor<CPL>([&](auto K) S5D_INL { cur[MI][+K] = (rowb || fix[K]) ? cur[MI][+K] : out[K]; });
+    } else {
+      sfor<CPL>([&](auto K) S5D_INL { cur[MI][+K] = out[K]; });
+    }
+  };
+
   for (int t = 1; t <= a.bt; ++t) {
     auto& hb = halo.rows[t & 1];
     sfor<R>([&](auto J) S5D_INL {
@@ -111,6 +122,7 @@ __device__ __forceinline__ void tile2d_body(const Tile2DArgs& a, const CoefPack<
         });
       }
     });
+    T sums[EXPR == EXPR_DIV ? M : 1][CPL];
     sfor<M>([&](auto MI) S5D_INL {
       T out[CPL];
       sfor<CPL>([&](auto K) S5D_INL {
@@ -129,16 +141,16 @@ __device__ __forceinline__ void tile2d_body(const Tile2DArgs& a, const CoefPack<
               }
             });
           });
-          out[K] = finish<EXPR>(acc.value(), cf);
+          out[K] = acc.value();
         }
       });
-      if constexpr (EDGE) {
-        const bool rowb = row0 + MI < R || row0 + MI >= I0 + R;
-        sfor<CPL>([&](auto K) S5D_INL { cur[MI][+K] = (rowb || fix[K]) ? cur[MI][+K] : out[K]; });
-      } else {
-        sfor<CPL>([&](auto K) S5D_INL { cur[MI][+K] = out[K]; });
+      if constexpr (EXPR == EXPR_DIV) {  // the sums of all rows first: one check of their range
+        sfor<CPL>([&](auto K) S5D_INL { sums[MI][K] = out[K]; });
+        if constexpr (MI == M - 1) fin(sums);
       }
+      if constexpr (EXPR != EXPR_DIV) keep(MI, out);
     });
+    if constexpr (EXPR == EXPR_DIV) sfor<M>([&](auto MI) S5D_INL { keep(MI, sums[MI]); });
   }
 
   // store the compute region: lanes from c_first on as vectors cut off by the

@@ -18,7 +18,7 @@ TileKernel2D make() {
   // double) and about 20 for the exchange and the loop
   constexpr int words = sizeof(T) / 4;
   constexpr int term = ACC ? 10 : 1;
-  constexpr int cell = EXPR == EXPR_GRADIENT ? 45 : term * npts(2, R, BOX) + (EXPR == EXPR_DIV ? 13 : 0);
+  constexpr int cell = EXPR == EXPR_GRADIENT ? 45 : term * npts(2, R, BOX) + (EXPR == EXPR_DIV ? 8 : 0);
   constexpr int instr = M * CPL * cell + (BOX ? M + 2 * R : M) * 2 * R * words + 20;
   // the wide float64 tiles of radius >= 2 take so many registers that a CU
   // holds one workgroup: nothing overlaps its exchange (measured a quarter)
