@@ -38,7 +38,8 @@ namespace s5d {
 template <typename T, int R, bool BOX, int BT, int CPL, int NW>
 struct Exchange3D {
   static constexpr bool ONCE = !BOX && 2 * BT * NW * 2 * R * 64 * CPL * static_cast<int>(sizeof(T)) <= 80 * 1024;
-  T rows[2][ONCE ? BT : 1][NW][2 * R][64 * CPL];
+  // aligned for the widest LDS accesses (a lane's cells are one)
+  alignas(16) T rows[2][ONCE ? BT : 1][NW][2 * R][64 * CPL];
 };
 
 template <typename T, int ACC, int EXPR, int R, bool BOX, int BT, int CPL, int M, int NW, int NR, bool EDGE>
