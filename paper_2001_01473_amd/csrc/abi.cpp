@@ -70,14 +70,11 @@ const Entry3D* find3d(int kind, int expr, int box, int r, int cpl, int m, int nw
 }
 
 // 3D defaults: depth and rows per wave (tile family: 2 rows per wave is the
-// 16-wave tile, 4 the 8-wave one), the best pair measured on MI355X at 512^3,
-// T = 1000, and a floor on the stream-block length where
-// the measured optimum lies above the chooser's pick (the float32 27-point
-// box: 64 planes, 620 GCell/s against 566 at the chooser's 19).  Compensated
-// accumulation is bound by arithmetic from the first level on.
+// 16-wave tile, 4 the 8-wave one) where the estimates below don't choose: the
+// best pair measured on MI355X at 512^3, T = 1000.  Compensated accumulation
+// is bound by arithmetic from the first level on.
 struct Default3D {
   int bt, m;
-  int hmin = 0;  // stream-block floor (planes), for extents of at least 4 * hmin
 };
 Default3D default_tuning3(int kind, int box, int r, int expr = 0) {
   if (expr == s5d::EXPR_DIV) return kind == KIND_F64 ? Default3D{2, 2} : Default3D{2, 4};
@@ -86,10 +83,9 @@ Default3D default_tuning3(int kind, int box, int r, int expr = 0) {
     if (r == 1) return box ? Default3D{2, 4} : Default3D{3, 2};
     return box ? Default3D{1, 2} : Default3D{2, 2};
   }
-  if (r == 1) return box ? Default3D{2, 4, 64} : Default3D{3, 4};
+  if (r == 1) return box ? Default3D{2, 4} : Default3D{3, 4};
   return box ? Default3D{1, 4} : Default3D{2, 4};
 }
-int default_bt3(int kind, int box, int r, int expr) { return default_tuning3(kind, box, r, expr).bt; }
 
 // Stencils whose direct kernel measured faster than every blocked variant
 // on MI355X.  3D at 512^3: the 125-point float32 box, the compensated
@@ -268,6 +264,120 @@ RoundSchedule schedule_rounds(int64_t T, int bt) {
 
 namespace {
 
+// What one launch of the 3D kernels takes (us): its start and the time for one
+// plane of a tile, with one workgroup on a CU (`alone`) and for each of two.
+// Least-squares fits to MI355X runs of 50 x 60 x 70 to 512^3, each at the block
+// lengths within 25 % of its best one (residuals 3 to 10 %, {1, 2} of the boxes
+// and the float64 star 11 to 13 %).
+struct Launch3D {
+  int kind, box, r, m, bt;
+  double start, alone, shared;
+};
+const Launch3D kLaunch3D[] = {
+    {KIND_F32, 0, 1, 4, 1, 2.5, 1.14, 1.13}, {KIND_F32, 0, 1, 4, 2, 5.9, 1.21, 1.13},
+    {KIND_F32, 0, 1, 4, 3, 5.4, 1.47, 1.19}, {KIND_F32, 0, 2, 2, 1, 4.7, 0.95, 0.95},
+    {KIND_F32, 0, 2, 4, 1, 5.2, 0.98, 0.94}, {KIND_F32, 0, 2, 4, 2, 10.1, 1.42, 1.48},
+    {KIND_F32, 1, 1, 2, 1, 5.0, 1.23, 1.32}, {KIND_F32, 1, 1, 2, 2, 9.5, 1.97, 1.87},
+    {KIND_F32, 1, 1, 2, 3, 8.4, 2.78, 2.89}, {KIND_F32, 1, 1, 4, 1, 4.8, 1.39, 1.18},
+    {KIND_F32, 1, 1, 4, 2, 11.8, 2.25, 1.77}, {KIND_F64, 0, 1, 2, 1, 2.0, 0.87, 0.81},
+    {KIND_F64, 0, 1, 2, 2, 3.8, 0.99, 0.81}, {KIND_F64, 0, 1, 2, 3, 6.5, 1.18, 0.90},
+    {KIND_F64, 0, 2, 2, 1, 3.1, 0.78, 0.68}, {KIND_F64, 0, 2, 2, 2, 9.3, 1.10, 1.17},
+    {KIND_F64, 1, 1, 2, 1, 3.6, 0.90, 0.83}, {KIND_F64, 1, 1, 2, 2, 7.6, 1.47, 1.48},
+    {KIND_F64, 1, 1, 2, 3, 6.6, 2.11, 2.14}, {KIND_F64, 1, 1, 4, 1, 4.0, 1.71, 1.85},
+    {KIND_F64, 1, 1, 4, 2, 8.9, 2.70, 2.62},
+};
+
+const Launch3D* find_launch3(int kind, int box, int r, int m, int bt) {
+  for (const Launch3D& l : kLaunch3D)
+    if (l.kind == kind && l.box == box && l.r == r && l.m == m && l.bt == bt) return &l;
+  return nullptr;
+}
+
+int64_t tiles3d(const s5d_plan* p, int rows, int cols, int bt, int r) {
+  const int64_t C1 = rows - 2LL * bt * r, C2 = s5d::compute_width(cols, bt, r, p->elem);
+  return ((p->d.interior[1] + C1 - 1) / C1) * ((p->d.interior[2] + C2 - 1) / C2);
+}
+
+// Turns of one workgroup alone that a launch's n = ceil(blocks / CUs)
+// workgroups come to on the busiest CU: two resident ones share its arithmetic,
+// the odd one runs alone.
+double turns3(int64_t n, double alone, double shared) {
+  return static_cast<double>(n % 2) * alone + static_cast<double>(n / 2 * 2) * shared;
+}
+
+// 3D stream blocks: a launch takes its turns times the h + 2*b_T*r planes of a
+// block, so launches of whole turns are what pays (27-point box, float64, 250 x
+// 301 x 190, b_T = 2: h = 20, two turns, 146 us; 25, one, 87; 32, one, 106).
+// At b_T = 1 a launch of many blocks is bound by memory instead: short blocks,
+// which read one window of planes, are faster (27-point float32 box with a
+// divisor, 400 x 300 x 200: 66 us at h = 8, 81 at 34).  The 7-point stars take 6
+// planes (512^3, float32 / float64: h = 6 293 / 493 us, h = 8 321 / 522), float64
+// 4 on grids that the caches hold in good part (400 x 300 x 200: h = 4 / 6 / 8 70 /
+// 77 / 79 us).
+int choose_chunk3(const s5d_plan* p, int rows, int cols, int m, int bt, int box, int r) {
+  const int64_t I0 = p->d.interior[0], ntiles = tiles3d(p, rows, cols, bt, r), cus = p->cus;
+  if (bt == 1 && ntiles * (I0 / 8) > 2 * cus) {
+    if (box || r > 1) return choose_chunk(I0, ntiles, 2 * cus, bt, r);
+    return p->kind == KIND_F64 && 2 * p->bytes <= 512e6 ? 4 : 6;
+  }
+  const Launch3D* l = find_launch3(p->kind, box, r, m, bt);
+  const double alone = l ? std::max(1.0, l->alone / l->shared) : 1.0;
+  int64_t best_h = I0;
+  double best = 1e300;
+  for (int64_t nch = 1; nch <= std::max<int64_t>(1, I0 / 2) && nch <= 4096; ++nch) {
+    const int64_t h = (I0 + nch - 1) / nch;
+    const int64_t n = (ntiles * ((I0 + h - 1) / h) + cus - 1) / cus;
+    const double cost = turns3(n, alone, 1.0) * static_cast<double>(h + 2LL * bt * r);
+    if (cost < best) {
+      best = cost;
+      best_h = h;
+    }
+  }
+  return static_cast<int>(std::min<int64_t>(best_h, INT32_MAX));
+}
+
+// Depth and rows per wave of a plain 3D stencil for the plan's grid and steps:
+// the pair whose rounds the table makes the shortest, no shallower than the
+// default, since the rounds of a batch's grids wait for each other (24 grids of
+// 32 to 160 a side at the depths that are fastest alone: 860 launches, 14.9 ms;
+// at the default ones 470, 12.5).  The 13-point stars take b_T = 1 from 128^3
+// on, where it does less work per cell and step (float64 160^3, 12 steps: 261 us,
+// b_T = 2 317), until a grid leaves the caches and memory bounds it (512^3, 6
+// steps: 3055, 2823).
+bool choose_depth3(const s5d_plan* p, int box, int r, Default3D* out) {
+  const int64_t least = r == 2 && p->bytes / p->elem >= 1 << 21 ? 1 : std::min<int64_t>(out->bt, p->d.steps);
+  const int64_t cus = p->cus;
+  if (p->expr != 0 || p->d.steps < 1) return false;
+  double best = 1e300;
+  for (const Launch3D& l : kLaunch3D) {
+    if (l.kind != p->kind || l.box != box || l.r != r || l.bt < least || l.bt > p->d.steps) continue;
+    const Entry3D* e = nullptr;
+    for (int i = 0; i < s5d::kRegistry3DSize && !e; ++i) {
+      const Entry3D& q = s5d::kRegistry3D[i];
+      if (q.dtype == p->kind && q.expr == 0 && q.box == box && q.r == r && q.m == l.m && q.bt == l.bt) e = &q;
+    }
+    if (!e) continue;
+    const int rows = e->m * e->nw, cols = 64 * e->cpl;
+    const int h = choose_chunk3(p, rows, cols, l.m, l.bt, box, r);
+    const int64_t nblk = (p->d.interior[0] + h - 1) / h;
+    auto launch_us = [&](int bt) {
+      const Launch3D* x = find_launch3(p->kind, box, r, l.m, bt);
+      if (!x) return 1e300;
+      const int64_t n = (tiles3d(p, rows, cols, bt, r) * nblk + cus - 1) / cus;
+      const double us = x->start + (h + 2.0 * bt * r) * turns3(n, x->alone, x->shared);
+      return std::max(us, 2.0 * static_cast<double>(p->bytes) / (2 * p->bytes > 256e6 ? 4e6 : 9e6));
+    };
+    const RoundSchedule s = schedule_rounds(p->d.steps, l.bt);
+    double us = s.n_full > 0 ? static_cast<double>(s.n_full) * launch_us(s.bt) : 0.0;
+    for (int k = 0; k < s.n_tail; ++k) us += launch_us(s.tail[k]);
+    if (us < best) {
+      best = us;
+      *out = {l.bt, l.m};
+    }
+  }
+  return best < 1e300;
+}
+
 // Direct kernels: one step per launch; the device coefficient table is made
 // here (the only device allocation of a plan).
 s5d_status plan_direct(s5d_plan* p, const s5d_tuning& req, int box, int r) {
@@ -391,8 +501,12 @@ s5d_status plan_3d(s5d_plan* p, const s5d_tuning& req, int box, int r) {
   // without an explicit shape, the default family if it is built
   int want_m = req.rows_per_wave;
   const int ex = p->expr;
+  const DeviceInfo dev = query_device();
+  p->cus = dev.ok && dev.cus > 0 ? dev.cus : 256;
+  Default3D def = default_tuning3(p->kind, box, r, ex);
   if (want_m == 0 && req.cells_per_lane == 0 && req.tile0 == 0 && req.tile1 == 0) {
-    const int m = default_tuning3(p->kind, box, r, ex).m;
+    if (req.bt == 0 && req.stream_chunk == 0) choose_depth3(p, box, r, &def);
+    const int m = def.m;
     for (int i = 0; i < s5d::kRegistry3DSize && want_m == 0; ++i) {
       const Entry3D& e = s5d::kRegistry3D[i];
       if (e.dtype == p->kind && e.expr == ex && e.box == box && e.r == r && e.m == m) want_m = m;
@@ -411,7 +525,7 @@ s5d_status plan_3d(s5d_plan* p, const s5d_tuning& req, int box, int r) {
     }
   }
   if (!fam) return fail(S5D_EUNSUPPORTED, "no 3D kernel for this stencil and tile shape");
-  int bt = req.bt > 0 ? req.bt : std::min(default_bt3(p->kind, box, r, ex), bt_cap);
+  int bt = req.bt > 0 ? req.bt : std::min(def.bt, bt_cap);
   if (bt > bt_cap)
     return fail(S5D_EUNSUPPORTED, "bt=" + std::to_string(bt) + " exceeds the deepest 3D kernel built (" +
                                       std::to_string(bt_cap) + ")");
@@ -424,16 +538,8 @@ s5d_status plan_3d(s5d_plan* p, const s5d_tuning& req, int box, int r) {
   const int B1 = fam->m * fam->nw, B2 = 64 * fam->cpl;
   int chunk = req.stream_chunk;
   if (chunk == 0) {
-    const DeviceInfo dev = query_device();
-    int occ = dev.ok ? p->by_bt3[bt].occupancy() : 0;
-    if (occ <= 0) occ = 1;
-    const int64_t C1 = B1 - 2LL * bt * r, C2 = s5d::compute_width(B2, bt, r, p->elem);
-    const int64_t ntiles = ((d.interior[1] + C1 - 1) / C1) * ((d.interior[2] + C2 - 1) / C2);
-    const int64_t slots = static_cast<int64_t>(dev.cus) * occ;  // resident workgroups
-    chunk = choose_chunk(d.interior[0], ntiles, slots, bt, r);
-    const Default3D def = default_tuning3(p->kind, box, r, ex);
-    if (def.hmin > 0 && bt == def.bt && fam->m == def.m && d.interior[0] >= 4LL * def.hmin)
-      chunk = std::max(chunk, def.hmin);
+    chunk = choose_chunk3(p, B1, B2, fam->m, bt, box, r);
+    p->chunk_auto = true;
   }
   if (chunk < 1) return fail(S5D_EINVAL, "stream_chunk must be >= 1");
   p->tun.bt = bt;
@@ -618,8 +724,14 @@ int fill_persist_round(const s5d_plan* p, const Persist2D& k, int bt, const void
 }
 
 int shared_chunk(const s5d_plan* p, int bt, double share) {
-  if (p->direct || !p->chunk_auto || p->d.ndim != 2 || bt < 1 || p->slots <= 0) return p->tun.stream_chunk;
   const int r = p->d.radius;
+  if (p->direct || !p->chunk_auto || bt < 1) return p->tun.stream_chunk;
+  if (p->d.ndim == 3) {
+    if (share >= 1.0) return p->tun.stream_chunk;
+    const int64_t cus = std::max<int64_t>(1, static_cast<int64_t>(p->cus * std::max(share, 0.0)));
+    return choose_chunk(p->d.interior[0], tiles3d(p, p->tun.tile0, p->tun.tile1, bt, r), cus, bt, r);
+  }
+  if (p->slots <= 0) return p->tun.stream_chunk;
   const int64_t C = s5d::compute_width(64 * p->tun.cells_per_lane, bt, r, p->elem);
   const int64_t ntiles = (p->d.interior[1] + C - 1) / C;
   const double all = static_cast<double>(p->slots);  // the plan's own variant (depth p->tun.bt)
