@@ -313,13 +313,16 @@ double turns3(int64_t n, double alone, double shared) {
 // divisor, 400 x 300 x 200: 66 us at h = 8, 81 at 34).  The 7-point stars take 6
 // planes (512^3, float32 / float64: h = 6 293 / 493 us, h = 8 321 / 522), float64
 // 4 on grids that the caches hold in good part (400 x 300 x 200: h = 4 / 6 / 8 70 /
-// 77 / 79 us).
+// 77 / 79 us).  So it is for the float32 7-point star, the lightest, at every depth
+// once both buffers pass 1 GB (b_T = 3, 60 steps: 512^3 h = 27 6.55 ms, 103 6.72;
+// 420 x 512 x 483 h = 27 5.44, 84 5.13).
 int choose_chunk3(const s5d_plan* p, int rows, int cols, int m, int bt, int box, int r) {
   const int64_t I0 = p->d.interior[0], ntiles = tiles3d(p, rows, cols, bt, r), cus = p->cus;
   if (bt == 1 && ntiles * (I0 / 8) > 2 * cus) {
     if (box || r > 1) return choose_chunk(I0, ntiles, 2 * cus, bt, r);
     return p->kind == KIND_F64 && 2 * p->bytes <= 512e6 ? 4 : 6;
   }
+  if (p->kind == KIND_F32 && !box && r == 1 && p->bytes > 500000000) return choose_chunk(I0, ntiles, 2 * cus, bt, r);
   const Launch3D* l = find_launch3(p->kind, box, r, m, bt);
   const double alone = l ? std::max(1.0, l->alone / l->shared) : 1.0;
   int64_t best_h = I0;
@@ -728,8 +731,11 @@ int shared_chunk(const s5d_plan* p, int bt, double share) {
   if (p->direct || !p->chunk_auto || bt < 1) return p->tun.stream_chunk;
   if (p->d.ndim == 3) {
     if (share >= 1.0) return p->tun.stream_chunk;
-    const int64_t cus = std::max<int64_t>(1, static_cast<int64_t>(p->cus * std::max(share, 0.0)));
-    return choose_chunk(p->d.interior[0], tiles3d(p, p->tun.tile0, p->tun.tile1, bt, r), cus, bt, r);
+    // three workgroups a CU (24 / 8 / 3 / 16 mixed 3D grids, one workgroup 14.1 /
+    // 16.2 / 4.0 / 6.7 ms, three 11.6 / 16.7 / 3.5 / 6.2; a server of 32 float32
+    // requests 566 / 594 GCell/s)
+    const int64_t units = std::max<int64_t>(1, static_cast<int64_t>(3 * p->cus * std::max(share, 0.0)));
+    return choose_chunk(p->d.interior[0], tiles3d(p, p->tun.tile0, p->tun.tile1, bt, r), units, bt, r);
   }
   if (p->slots <= 0) return p->tun.stream_chunk;
   const int64_t C = s5d::compute_width(64 * p->tun.cells_per_lane, bt, r, p->elem);
