@@ -128,8 +128,8 @@ RoundModel model_round2d(const s5d_plan* p, int bt) {
     }
   m.gm = (rows_read * cols_read + static_cast<double>(I0) * cols_written) * w;
   if (p->expr == EXPR_VARCOEF) {
-    // the weights of every cell, once per round from HBM (the levels re-read
-    // them from the caches)
+    // the weights of every cell, once per round from HBM (the deeper
+    // levels take them from LDS)
     const int n = p->d.shape == S5D_BOX ? (2 * r + 1) * (2 * r + 1) : 4 * r + 1;
     m.gm += static_cast<double>(n) * static_cast<double>(I0) * static_cast<double>(I1) * w;
   }
