@@ -11,7 +11,7 @@ from gpu_util import say, torch
 pytestmark = pytest.mark.gpu
 
 # inside the reciprocal's range, at its ends, below one, negative, far outside
-DIVISORS = [118.0, 1.0, 3.0, -7.25, 0.7, 2.0 ** 60, 1.1 * 2.0 ** 60, 1e30, 1e-30]
+DIVISORS = [118.0, 1.0, 3.0, -7.25, 0.7, 1.3 * 2.0 ** -20, 2.0 ** -21, 2.0 ** 60, 1.1 * 2.0 ** 60, 1e30, 1e-30]
 
 
 def _values(dtype, shape, seed):
