@@ -235,12 +235,16 @@ typedef struct s5d_tune_report {
  * every compiled variant of the stencil with a ladder of stream block
  * lengths, rank them by the model, time the best top_k on the GPU (two full
  * rounds each, on scratch buffers the tuner allocates and frees), and keep
- * the fastest, or the library's default if none beats it.  top_k = 0 trusts
- * the model alone.  The winner goes to *best and, unless it is the choice a
- * plan without tuning gets already, into the process-wide cache,
+ * the fastest, or what a plan without tuning runs (on resident tiles, where
+ * the library takes them) if none beats that.  top_k = 0 trusts the model
+ * alone.  The winner goes to *best and, unless it is the choice a plan without
+ * tuning gets already, into the process-wide cache,
  * from which s5d_plan_create takes it whenever it is given no tuning for a
  * descriptor with the same stencil, dtype, accumulation and power-of-two
- * bucket of every extent.  Synchronous on `stream`. */
+ * bucket of every extent.  Such a plan may still run on resident tiles (see
+ * s5d_plan_query), unless the entry was timed against them for its extents.
+ * If the library's own choice wins, a cached entry that it beat is dropped,
+ * and *best holds that choice's streaming parameters.  Synchronous on `stream`. */
 s5d_status s5d_autotune(const s5d_desc *desc, int32_t top_k, void *stream, s5d_tuning *best,
                         s5d_tune_report *report);
 

@@ -882,18 +882,19 @@ s5d_status s5d_plan_create(const s5d_desc* desc, const s5d_tuning* tuning, s5d_p
   // is taken if one is cached and still valid; else the library's defaults
   s5d_tuning cached;
   s5d_status st = S5D_EINVAL;
-  bool from_cache = false;
+  bool streams = false;  // tuned and found faster than resident tiles
   s5d::load_default_tuning();
-  if (!tuning && s5d::tune_cache_lookup(d, &cached)) {
+  if (!tuning && s5d::tune_cache_lookup(d, &cached, &streams)) {
     st = d.ndim == 2 ? plan_2d(p, cached, box, r) : plan_3d(p, cached, box, r);
     if (st != S5D_OK) {
       g_last_error.clear();
       reset();
+      streams = false;
     } else {
       // the library chose it (through the tuner), not the caller: batches and
-      // servers may still size the stream blocks for a grid's share
+      // servers may still size the stream blocks for a grid's share, and a
+      // small grid may run on resident tiles
       p->chunk_auto = true;
-      from_cache = true;
     }
   }
   const bool no_blocking = req.bt <= 1 && req.cells_per_lane == 0 && req.rows_per_wave == 0 && req.tile0 == 0 &&
@@ -925,7 +926,7 @@ s5d_status s5d_plan_create(const s5d_desc* desc, const s5d_tuning* tuning, s5d_p
     }
   }
   if (st == S5D_OK) p->tun.kernel = p->direct ? S5D_KERNEL_DIRECT : S5D_KERNEL_BLOCKED;
-  p->tile_ok = d.ndim == 2 && !from_cache && req.kernel == S5D_KERNEL_AUTO && no_blocking && req.bt == 0 &&
+  p->tile_ok = d.ndim == 2 && !streams && req.kernel == S5D_KERNEL_AUTO && no_blocking && req.bt == 0 &&
                s5d::tile_kernel2d(p->kind, p->expr, r, box != 0, 0) != nullptr;
   if (p->tile_ok && p->direct) p->cus = query_device().cus;
   if (st != S5D_OK) {
@@ -1041,6 +1042,13 @@ s5d_status s5d_error_norms_noalloc(const void* got, int32_t got_dtype, const voi
                               s5d::error_norms_parts(n), static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return device_fail(e, "error-norm launch");
   return S5D_OK;
+}
+
+int32_t s5d_internal_rounds(const s5d_plan* plan, double share, int32_t* tile_rows, int32_t* tile_cols) {
+  const s5d::Rounds r = s5d::choose_rounds(plan, share);
+  *tile_rows = r.tile ? r.tile->rows : 0;
+  *tile_cols = r.tile ? r.tile->cols : 0;
+  return static_cast<int32_t>(r.bt.size());
 }
 
 }  // extern "C"

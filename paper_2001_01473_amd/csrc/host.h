@@ -102,11 +102,16 @@ s5d_status check_buffers(const s5d_plan* p, const void* buf0, const void* buf1);
 s5d_status model_plan(const s5d_plan* p, s5d_model* out);
 
 // The autotuned blocking cached for this descriptor's stencil, dtype,
-// accumulation and extent bucket, if any.
-bool tune_cache_lookup(const s5d_desc& d, s5d_tuning* tun);
+// accumulation and extent bucket, if any; *streams: it was measured for these
+// very extents to be faster than resident tiles.
+bool tune_cache_lookup(const s5d_desc& d, s5d_tuning* tun, bool* streams);
 
 // Load the autotuner's shipped choices once per process: the file named by
 // S5D_TUNING_FILE (empty: none), else tuning_gfx950.txt beside the library.
 void load_default_tuning();
 
 }  // namespace s5d
+
+// For the tests, not part of the ABI: the rounds of a plan's sweep, and the
+// resident tile they run on (0 x 0: the plan's own kernels).
+extern "C" int32_t s5d_internal_rounds(const s5d_plan* plan, double share, int32_t* tile_rows, int32_t* tile_cols);

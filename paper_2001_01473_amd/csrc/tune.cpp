@@ -280,11 +280,15 @@ Key key_of(const s5d_desc& d) {
 
 // The winner's stream-block length was measured for one set of extents: it is
 // kept for exactly those, while other extents of the same bucket have it
-// chosen again for their own size (stream_chunk = 0).
+// chosen again for their own size (stream_chunk = 0).  So is `streams`: the
+// winner was timed against what a plan without an entry runs, resident tiles
+// included, and is faster.  Entries that weren't (ranked by the model alone, or
+// from a file written before the field was) leave that choice to the estimate.
 struct CacheEntry {
   s5d_tuning tun;
   double sec_per_step;
   int64_t interior[3];
+  bool streams;
 };
 
 std::mutex g_cache_mu;
@@ -316,7 +320,7 @@ void load_default_tuning() {
   });
 }
 
-bool tune_cache_lookup(const s5d_desc& d, s5d_tuning* tun) {
+bool tune_cache_lookup(const s5d_desc& d, s5d_tuning* tun, bool* streams) {
   std::lock_guard<std::mutex> lk(g_cache_mu);
   auto it = g_cache.find(key_of(d));
   if (it == g_cache.end()) return false;
@@ -324,6 +328,7 @@ bool tune_cache_lookup(const s5d_desc& d, s5d_tuning* tun) {
   bool same = true;
   for (int a = 0; a < d.ndim; ++a) same = same && it->second.interior[a] == d.interior[a];
   if (!same) tun->stream_chunk = 0;
+  *streams = same && it->second.streams;
   return true;
 }
 
@@ -339,14 +344,34 @@ struct Candidate {
   double model = 0, measured = -1;
 };
 
-// Time one candidate: a sweep of two full rounds (2*b_T steps) on scratch
-// buffers, after one warm-up; returns seconds per time step.
-s5d_status measure(const s5d_desc& d, const s5d_tuning& tun, void* b0, void* b1, const void* fields, hipStream_t st,
-                   int reps, double* sec_per_step) {
-  s5d_desc dd = d;
-  dd.steps = 2LL * tun.bt;
+// A plan that leaves the blocking to the library: its parameters, and whether
+// its sweep runs on resident tiles instead of the kernels they describe.
+struct Choice {
+  s5d_tuning tun;
+  bool tiles = false, direct = false;
+  int64_t bytes = 0;
+};
+
+s5d_status library_choice(const s5d_desc& d, const s5d_tuning* tuning, Choice* c) {
   s5d_plan* p = nullptr;
-  s5d_status rc = s5d_plan_create(&dd, &tun, &p);
+  const s5d_status rc = s5d_plan_create(&d, tuning, &p);
+  if (rc != S5D_OK) return rc;
+  c->tun = p->tun;
+  c->tiles = s5d::choose_rounds(p, 1.0).tile != nullptr;
+  c->direct = p->direct;
+  c->bytes = p->bytes;
+  s5d_plan_destroy(p);
+  return S5D_OK;
+}
+
+// Time one choice: a sweep of `steps` steps on scratch buffers, after one
+// warm-up; returns seconds per time step.
+s5d_status measure(const s5d_desc& d, const s5d_tuning* tun, int64_t steps, void* b0, void* b1, const void* fields,
+                   hipStream_t st, int reps, double* sec_per_step) {
+  s5d_desc dd = d;
+  dd.steps = steps;
+  s5d_plan* p = nullptr;
+  s5d_status rc = s5d_plan_create(&dd, tun, &p);
   if (rc != S5D_OK) return rc;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   hipError_t e = hipEventCreate(&e0);
@@ -385,21 +410,23 @@ s5d_status s5d_autotune(const s5d_desc* desc, int32_t top_k, void* stream, s5d_t
   if (top_k < 0) return fail(S5D_EINVAL, "top_k must be >= 0");
   if (report && report->struct_size < sizeof(s5d_tune_report))
     return fail(S5D_EINVAL, "report->struct_size too small");
-  // the library's own choice first: it validates the descriptor and is the
-  // baseline the tuner must match
-  s5d_plan* base = nullptr;
-  s5d_status rc = s5d_plan_create(desc, nullptr, &base);
+  // what a plan without a tuning gets now (`base`, from the cache if that holds
+  // an entry) and what it would get without the cache (`lib`): the first
+  // validates the descriptor, and the tuner must match both
+  s5d_tuning none;
+  std::memset(&none, 0, sizeof(none));
+  none.struct_size = sizeof(s5d_tuning);
+  Choice base, lib;
+  s5d_status rc = library_choice(*desc, nullptr, &base);
+  if (rc == S5D_OK) rc = library_choice(*desc, &none, &lib);
   if (rc != S5D_OK) return rc;
-  const int64_t bytes = base->bytes;
-  s5d_tuning base_tun;
-  std::memset(&base_tun, 0, sizeof(base_tun));
-  base_tun.struct_size = sizeof(s5d_tuning);
-  (void)s5d_plan_query(base, &base_tun, nullptr);
-  const bool base_direct = base->direct;
-  s5d_plan_destroy(base);
-  if (base_direct) {
+  s5d_tuning entry;
+  bool streams = false;
+  const bool cached = s5d::tune_cache_lookup(*desc, &entry, &streams);
+  const int64_t bytes = base.bytes;
+  if (base.direct) {
     // a direct kernel has no blocking parameters: nothing to choose
-    *best = base_tun;
+    *best = base.tun;
     if (report) {
       report->n_candidates = 1;
       report->n_measured = 0;
@@ -469,7 +496,7 @@ s5d_status s5d_autotune(const s5d_desc* desc, int32_t top_k, void* stream, s5d_t
   cands.swap(uniq);
 
   Candidate* win = &cands[0];
-  bool base_won = false;
+  enum { CANDIDATE, BASE, LIBRARY } winner = CANDIDATE;
   double base_measured = -1;
   int n_measured = 0;
   if (top_k > 0 && desc->steps > 0) {
@@ -479,9 +506,9 @@ s5d_status s5d_autotune(const s5d_desc* desc, int32_t top_k, void* stream, s5d_t
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e = hipMalloc(&b0, static_cast<size_t>(bytes));
     if (e == hipSuccess) e = hipMalloc(&b1, static_cast<size_t>(bytes));
-    if (e == hipSuccess) e = hipMemsetAsync(b0, 0, static_cast<size_t>(bytes), st);  // timing does not depend on values
+    if (e == hipSuccess) e = hipMemsetAsync(b0, 0, static_cast<size_t>(bytes), st);  // a divided sum of zero takes the same path as ordinary ones
     if (e == hipSuccess && desc->expr == S5D_EXPR_VARCOEF) {
-      // per-cell weights for the timing runs (values do not matter either)
+      // per-cell weights for the timing runs (their values do not matter)
       const int64_t np = box ? (desc->ndim == 2 ? 1LL : (2LL * desc->radius + 1)) * (2LL * desc->radius + 1) *
                                    (2LL * desc->radius + 1)
                              : 2LL * desc->radius * desc->ndim + 1;
@@ -498,7 +525,7 @@ s5d_status s5d_autotune(const s5d_desc* desc, int32_t top_k, void* stream, s5d_t
     const int reps = 3;
     double best_t = 1e300;
     for (size_t i = 0; i < cands.size() && static_cast<int>(i) < top_k; ++i) {
-      rc = measure(*desc, cands[i].tun, b0, b1, fl, st, reps, &cands[i].measured);
+      rc = measure(*desc, &cands[i].tun, 2LL * cands[i].tun.bt, b0, b1, fl, st, reps, &cands[i].measured);
       if (rc != S5D_OK) break;
       ++n_measured;
       if (cands[i].measured < best_t) {
@@ -506,25 +533,42 @@ s5d_status s5d_autotune(const s5d_desc* desc, int32_t top_k, void* stream, s5d_t
         win = &cands[i];
       }
     }
-    if (rc == S5D_OK) rc = measure(*desc, base_tun, b0, b1, fl, st, reps, &base_measured);
+    // two rounds of streaming kernels, up to 200 steps of resident tiles, whose
+    // rounds depend on their number
+    auto measure_choice = [&](const Choice& c, const s5d_tuning* none_or_cache, double* sec) {
+      return c.tiles ? measure(*desc, none_or_cache, std::min<int64_t>(desc->steps, 200), b0, b1, fl, st, reps, sec)
+                     : measure(*desc, &c.tun, c.direct ? 2 : 2LL * c.tun.bt, b0, b1, fl, st, reps, sec);
+    };
+    double lib_measured = -1;
+    if (rc == S5D_OK) rc = measure_choice(base, nullptr, &base_measured);
+    if (cached && rc == S5D_OK) rc = measure_choice(lib, &none, &lib_measured);
+    if (!cached) lib_measured = base_measured;
     (void)hipStreamSynchronize(st);
     (void)hipFree(b0);
     (void)hipFree(b1);
     if (fl) (void)hipFree(fl);
     if (rc != S5D_OK) return rc;
-    if (base_measured > 0 && base_measured < best_t) {
-      // the library's own choice stays if no candidate beats it
-      cands.push_back(Candidate{base_tun, 0.0, base_measured});
+    // the library's own choice, or the cached one, stays if no candidate beats it
+    if (lib_measured < best_t) {
+      best_t = lib_measured;
+      winner = LIBRARY;
+    }
+    if (base_measured < best_t) winner = BASE;
+    if (winner != CANDIDATE) {
+      cands.push_back(winner == LIBRARY ? Candidate{lib.tun, 0.0, lib_measured} : Candidate{base.tun, 0.0, base_measured});
       win = &cands.back();
-      base_won = true;
     }
   }
   *best = win->tun;
-  if (!base_won) {
+  {
     // (the library's own choice needs no entry: plans without one get it)
     std::lock_guard<std::mutex> lk(s5d::g_cache_mu);
-    s5d::g_cache[s5d::key_of(*desc)] =
-        s5d::CacheEntry{win->tun, win->measured, {desc->interior[0], desc->interior[1], desc->interior[2]}};
+    if (winner == LIBRARY) {
+      s5d::g_cache.erase(s5d::key_of(*desc));
+    } else if (winner == CANDIDATE) {
+      s5d::g_cache[s5d::key_of(*desc)] =
+          s5d::CacheEntry{win->tun, win->measured, {desc->interior[0], desc->interior[1], desc->interior[2]}, n_measured > 0};
+    }
   }
   if (report) {
     report->n_candidates = static_cast<int32_t>(cands.size());
@@ -544,16 +588,16 @@ s5d_status s5d_tune_cache_save(const char* path) {
   std::lock_guard<std::mutex> lk(s5d::g_cache_mu);
   std::fprintf(f, "# stencil5d tuning cache v2: ndim shape radius dtype accum expr b0 b1 b2 : bt tile0 tile1 "
                   "stream_chunk cells_per_lane rows_per_wave : seconds_per_step : interior0 interior1 "
-                  "interior2 (the extents stream_chunk was measured for)\n");
+                  "interior2 (the extents stream_chunk was measured for) : 1 if faster there than resident tiles\n");
   for (const auto& kv : s5d::g_cache) {
     const auto& k = kv.first;
     const s5d_tuning& t = kv.second.tun;
     const int64_t* in = kv.second.interior;
-    std::fprintf(f, "%d %d %d %d %d %d %d %d %d : %d %d %d %d %d %d : %.9g : %lld %lld %lld\n", std::get<0>(k),
+    std::fprintf(f, "%d %d %d %d %d %d %d %d %d : %d %d %d %d %d %d : %.9g : %lld %lld %lld : %d\n", std::get<0>(k),
                  std::get<1>(k), std::get<2>(k), std::get<3>(k), std::get<4>(k), std::get<5>(k), std::get<6>(k),
                  std::get<7>(k), std::get<8>(k), t.bt, t.tile0, t.tile1, t.stream_chunk, t.cells_per_lane, t.rows_per_wave,
                  kv.second.sec_per_step, static_cast<long long>(in[0]), static_cast<long long>(in[1]),
-                 static_cast<long long>(in[2]));
+                 static_cast<long long>(in[2]), kv.second.streams ? 1 : 0);
   }
   const bool ok = std::fclose(f) == 0;
   return ok ? S5D_OK : fail(S5D_EINVAL, std::string("write failed: ") + path);
@@ -572,9 +616,10 @@ s5d_status s5d_tune_cache_load(const char* path) {
     int k[9], t[6];
     double sec = 0;
     long long in[3] = {0, 0, 0};
-    if (std::sscanf(line, "%d %d %d %d %d %d %d %d %d : %d %d %d %d %d %d : %lf : %lld %lld %lld", &k[0], &k[1],
+    int streams = 0;  // absent in files written before the field was
+    if (std::sscanf(line, "%d %d %d %d %d %d %d %d %d : %d %d %d %d %d %d : %lf : %lld %lld %lld : %d", &k[0], &k[1],
                     &k[2], &k[3], &k[4], &k[5], &k[6], &k[7], &k[8], &t[0], &t[1], &t[2], &t[3], &t[4], &t[5], &sec,
-                    &in[0], &in[1], &in[2]) != 19) {
+                    &in[0], &in[1], &in[2], &streams) < 19) {
       bad = true;
       break;
     }
@@ -588,7 +633,8 @@ s5d_status s5d_tune_cache_load(const char* path) {
     tun.cells_per_lane = t[4];
     tun.rows_per_wave = t[5];
     loaded[s5d::Key{k[0], k[1], k[2], k[3], k[4], k[5], k[6], k[7], k[8]}] =
-        s5d::CacheEntry{tun, sec, {static_cast<int64_t>(in[0]), static_cast<int64_t>(in[1]), static_cast<int64_t>(in[2])}};
+        s5d::CacheEntry{tun, sec, {static_cast<int64_t>(in[0]), static_cast<int64_t>(in[1]), static_cast<int64_t>(in[2])},
+                        streams == 1};
   }
   std::fclose(f);
   if (bad) return fail(S5D_EINVAL, std::string("malformed tuning cache: ") + path);
