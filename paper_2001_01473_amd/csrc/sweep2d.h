@@ -72,6 +72,20 @@ constexpr bool folded_coef2d(int ci) {
   return BOX ? ci % (2 * R + 1) != R : (ci >= R && ci <= 3 * R && ci != 2 * R);
 }
 
+// A box of radius 3 or 4 holds its 49 or 81 coefficients in scalar registers.
+// At some depths the scheduler forms the boundary masks of all levels at once,
+// and the coefficients spill to vector lanes and are read back for every term
+// (float32 radius 3, b_T = 4: 23694 v_readlane in the loop, 263 with a fence
+// before each level's selection).  Fenced where that measured faster; two rounds at
+// 3000 x 4100, us without / with it: float32 radius 3, b_T = 4 1285 / 400, 5 1594 /
+// 570 (3 319 / 328); radius 4, b_T = 2 461 / 383, 3 632 / 537, 5 2368 / 1187 (4 1717 /
+// 2802); float64 radius 4 312 / 280 (radius 3, b_T = 1 145 / 151, 2 251 / 261).
+template <typename T>
+constexpr bool fence_masks2d(int r, int bt) {
+  if (sizeof(T) == 8) return r == 4;
+  return r == 3 ? bt == 4 || bt == 5 : r == 4 && (bt == 2 || bt == 3 || bt == 5);
+}
+
 template <typename T, int ACC, int EXPR, int R, bool BOX, int BT, int CPL, int NR, bool EDGE>
 __device__ __forceinline__ void sweep2d_body(const Sweep2DArgs& a, const CoefPack<T, ncoef(2, R, BOX, EXPR)>& cf,
                                              int lane, int tile, int row_a, int row_b,
@@ -228,6 +242,7 @@ __device__ __forceinline__ void sweep2d_body(const Sweep2DArgs& a, const CoefPac
         });
 
 
+        if constexpr (EDGE && BOX && fence_masks2d<T>(R, BT)) __builtin_amdgcn_sched_barrier(0);
         if constexpr (EDGE && lv < BT) {
           // the last level is only stored, and boundary cells are never stored;
           // without a branch, so that the LDS reads move ahead of the levels
