@@ -221,6 +221,22 @@ int choose_chunk(int64_t I0, int64_t ntiles, int64_t slots, int bt, int r) {
   return static_cast<int>(std::min<int64_t>(best_h, INT32_MAX));
 }
 
+// Per-cell weights take so much LDS that a CU may hold fewer waves than SIMDs.
+// Each then runs by itself and a launch lasts whole turns: where blocks of h rows
+// take up to two, somewhat longer ones that take one are faster (9-point star
+// float32, b_T = 4, two waves a CU, 6965 x 8, 20 steps: h = 13, 536 blocks, 383 us;
+// 14, 504, 239).
+int one_turn(int64_t I0, int64_t ntiles, int64_t slots, int h, int warmup) {
+  auto blocks = [&](int rows) {
+    const s5d::Bands2D g = s5d::make_bands2d(static_cast<int>(I0), rows);
+    return ntiles * g.nb * (g.n1 + g.n2);
+  };
+  if (blocks(h) <= slots || blocks(h) > 2 * slots) return h;
+  for (int k = h + 1; k + warmup < 2 * (h + warmup) && k <= I0; ++k)
+    if (blocks(k) <= slots) return k;
+  return h;
+}
+
 // A whole sweep as (n_full rounds of bt) followed by up to three shorter
 // rounds; the total round count has the parity of T, so the result lands in
 // buffer T % 2 (AN5D "Host Code").
@@ -479,12 +495,14 @@ s5d_status plan_2d(s5d_plan* p, const s5d_tuning& req, int box, int r) {
     int occ = dev.ok ? p->by_bt[bt].occupancy() : 0;
     if (occ <= 0) occ = 2;
     p->cus = dev.cus;
-    p->slots = static_cast<int64_t>(dev.cus) * occ * s5d::kWavesPerBlock;
+    p->slots = static_cast<int64_t>(dev.cus) * occ * p->by_bt[bt].waves;
   }
   if (chunk == 0) {
     const int64_t C = s5d::compute_width(64 * cpl, bt, r, p->elem);
     const int64_t ntiles = (d.interior[1] + C - 1) / C;
     chunk = choose_chunk(d.interior[0], ntiles, p->slots, bt, r);
+    if (ex == s5d::EXPR_VARCOEF && p->slots <= int64_t{4} * p->cus)
+      chunk = one_turn(d.interior[0], ntiles, p->slots, chunk, 2 * bt * r);
     p->chunk_auto = true;
   }
   if (chunk < 1) return fail(S5D_EINVAL, "stream_chunk must be >= 1");

@@ -139,6 +139,8 @@ struct BlockMap {
 using FillItem2DFn = int (*)(void* item, const Round2D& rd);  // returns the grid's workgroups
 using LaunchBatchFn = hipError_t (*)(const void* items, const BlockMap* map, int nblocks, hipStream_t stream);
 
+constexpr int kWavesPerBlock = 4;  // of the 2D kernels but those with per-cell weights
+
 struct Kernel2D {
   Launch2DFn launch;
   Occupancy2DFn occupancy;
@@ -148,6 +150,7 @@ struct Kernel2D {
   FillItem2DFn fill_item;
   LaunchBatchFn launch_batch;
   int item_bytes;
+  int waves = kWavesPerBlock;  // per workgroup, the unit of `occupancy`
 };
 
 // One compiled 2D kernel variant.  The build enumerates the variants (one
@@ -231,7 +234,5 @@ struct HaloItem {
 };
 int64_t halo_cells(int ndim, const int64_t* padded, int r);
 hipError_t launch_halo_copy_batch(const HaloItem* items, int n, int64_t max_cells, hipStream_t stream);
-
-constexpr int kWavesPerBlock = 4;
 
 }  // namespace s5d

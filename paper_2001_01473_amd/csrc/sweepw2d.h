@@ -340,15 +340,13 @@ hipError_t launch_sweepw2d(const Round2D& rd) {
   return hipGetLastError();
 }
 
-// Resident workgroups of kWavesPerBlock waves, the unit of the stream-block
-// chooser, rounded up.
 template <typename T, int OP, int R, bool BOX, int BT, int CPL, int NR>
 int occupancy_sweepw2d() {
   int nb = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, sweepw2d_kernel<T, OP, R, BOX, BT, CPL, NR>,
                                                    64 * win_waves<OP>(), 0) != hipSuccess)
     return 0;
-  return (nb * win_waves<OP>() + kWavesPerBlock - 1) / kWavesPerBlock;
+  return nb;
 }
 
 // Window kernels have no batched entry point: batches and servers reject
@@ -362,7 +360,8 @@ Kernel2D make_kernelw2d() {
                   64 * CPL,
                   nullptr,
                   nullptr,
-                  0};
+                  0,
+                  win_waves<OP>()};
 }
 
 }  // namespace s5d

@@ -98,7 +98,7 @@ int64_t clip(int64_t a, int64_t b, int64_t n) { return std::max<int64_t>(0, std:
 struct RoundModel {
   double ops = 0, gm = 0, lds = 0;
   int64_t wgs = 0;
-  int wg_per_cu = 2;
+  double wg_per_cu = 2;  // 2D: of kWavesPerBlock waves
 };
 
 RoundModel model_round2d(const s5d_plan* p, int bt) {
@@ -136,7 +136,7 @@ RoundModel model_round2d(const s5d_plan* p, int bt) {
   m.ops = rows_comp * W * ntiles * ops_per_cell(p, cpl);
   m.wgs = (ntiles * blocks + kWavesPerBlock - 1) / kWavesPerBlock;
   const int occ = p->by_bt[bt].occupancy ? p->by_bt[bt].occupancy() : 0;
-  m.wg_per_cu = occ > 0 ? occ : 2;
+  m.wg_per_cu = occ > 0 ? static_cast<double>(occ * p->by_bt[bt].waves) / kWavesPerBlock : 2.0;
   return m;
 }
 
