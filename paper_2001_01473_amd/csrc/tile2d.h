@@ -79,7 +79,7 @@ __device__ __forceinline__ void tile2d_body(const Tile2DArgs& a, const CoefPack<
   const bool grid_rows = row0 + M > R && row0 < I0 + R;  // does this wave hold interior rows?
   const int wu = w > 0 ? w - 1 : w, wd = w + 1 < NW ? w + 1 : w;
 
-  const Finish<EXPR, T, CoefPack<T, ncoef(2, R, BOX, EXPR)>> fin(cf);
+  Finish<EXPR, T, CoefPack<T, ncoef(2, R, BOX, EXPR)>> fin(cf);
   // row MI takes its new values, except the cells that keep theirs
   auto keep = [&](auto MI, const T (&out)[CPL]) S5D_INL {
     if constexpr (EDGE) {
