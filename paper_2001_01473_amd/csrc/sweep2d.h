@@ -231,7 +231,7 @@ __device__ __forceinline__ void sweep2d_body(const Sweep2DArgs& a, const CoefPac
           add_row(ic<R>{}, v, K, std::false_type{});
           out[K] = v.value();
         });
-        fin.once(out);
+        fin(out);
         // 2. output p+R starts in the freed slot (d0 = -R)
         sfor<CPL>([&](auto K) S5D_INL { add_row(ic<-R>{}, A[so][K], K, std::true_type{}); });
         // 3. outputs p+R-1 .. p-R+1 (d0 = -R+1 .. R-1)

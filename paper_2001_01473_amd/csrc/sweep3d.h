@@ -203,7 +203,7 @@ __device__ __forceinline__ void sweep3d_body(const Sweep3DArgs& a, const CoefPac
             if constexpr (CELLWISE) out[MI][K] /= fin.c0;
           });
         });
-        if constexpr (!CELLWISE) fin.once(out);
+        if constexpr (!CELLWISE) fin(out);
         if constexpr (EDGE && lv < BT) {
           // boundary cells take the value plane o had when it arrived here (R
           // steps ago); then the slot records plane p
@@ -380,7 +380,7 @@ __device__ __forceinline__ void sweep3d_body(const Sweep3DArgs& a, const CoefPac
             if constexpr (CELLWISE) out[MI][K] /= fin.c0;
           });
         });
-        if constexpr (!CELLWISE) fin.once(out);
+        if constexpr (!CELLWISE) fin(out);
         sfor<M>([&](auto MI) S5D_INL {
           sfor<CPL>([&](auto K) S5D_INL { add_plane(ic<-R>{}, A[so][MI][K], MI, K, std::true_type{}); });
         });

@@ -80,6 +80,9 @@ __device__ __forceinline__ void tile2d_body(const Tile2DArgs& a, const CoefPack<
   const int wu = w > 0 ? w - 1 : w, wd = w + 1 < NW ? w + 1 : w;
 
   Finish<EXPR, T, CoefPack<T, ncoef(2, R, BOX, EXPR)>> fin(cf);
+  // scalar registers are short here (13 points: 242 reads of spilled ones in the
+  // float32 step, 76 with the bound in a vector register)
+  if constexpr (EXPR == EXPR_DIV) fin.least = to_vgpr(fin.least);
   // row MI takes its new values, except the cells that keep theirs
   auto keep = [&](auto MI, const T (&out)[CPL]) S5D_INL {
     if constexpr (EDGE) {
