@@ -79,10 +79,11 @@ constexpr bool folded_coef2d(int ci) {
 // before each level's selection).  Fenced where that measured faster; two rounds at
 // 3000 x 4100, us without / with it: float32 radius 3, b_T = 4 1285 / 400, 5 1594 /
 // 570 (3 319 / 328); radius 4, b_T = 2 461 / 383, 3 632 / 537, 5 2368 / 1187 (4 1717 /
-// 2802); float64 radius 4 312 / 280 (radius 3, b_T = 1 145 / 151, 2 251 / 261).
+// 2802).  Not in float64: radius 3, b_T = 1 145 / 151, 2 251 / 261; radius 4 312 / 280,
+// but 255 / 273 at 6117 x 13 (8 steps).
 template <typename T>
 constexpr bool fence_masks2d(int r, int bt) {
-  if (sizeof(T) == 8) return r == 4;
+  if (sizeof(T) == 8) return false;
   return r == 3 ? bt == 4 || bt == 5 : r == 4 && (bt == 2 || bt == 3 || bt == 5);
 }
 
