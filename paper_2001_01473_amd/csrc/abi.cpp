@@ -397,6 +397,71 @@ bool choose_depth3(const s5d_plan* p, int box, int r, Default3D* out) {
   return best < 1e300;
 }
 
+// Blocks of the marching kernel for a plan's grid.  A block of h planes takes h +
+// 2r steps, rounded up to the unrolled 2r; the launch lasts as long as the
+// fullest CU (measured: 256^3 float32 radius 2, 240 blocks of 32 planes 43 us,
+// 480 of 16 46, 960 of 8 48, 330 of 24 58), less sharply so from four blocks per
+// CU on.  Chosen once, when the plan is made.
+struct MarchBlocks {
+  int planes = 1;
+  double steps = 0, turns = 0;  // of a block; of the fullest CU
+};
+
+MarchBlocks march_blocks(const s5d_plan* p, const Kernel3D& k) {
+  const int64_t r = p->d.radius, I0 = p->d.interior[0];
+  const int64_t tiles = tiles3d(p, k.m * k.nw, 64 * k.cpl, 1, static_cast<int>(r));
+  MarchBlocks best;
+  for (int64_t nb = 1; nb <= std::min<int64_t>((I0 + r - 1) / r, 4096); ++nb) {
+    const int64_t h = (I0 + nb - 1) / nb;
+    const double steps = static_cast<double>((h + 4 * r - 1) / (2 * r) * (2 * r));
+    const double x = static_cast<double>(tiles * ((I0 + h - 1) / h)) / p->cus;  // blocks per CU
+    const double turns = x <= 1.0 ? 1.0 : (x < 4.0 ? std::ceil(x) : x + 0.5);
+    if (nb == 1 || steps * turns < best.steps * best.turns) best = MarchBlocks{static_cast<int>(h), steps, turns};
+  }
+  return best;
+}
+
+// What one step of a plain 3D star takes (us) on the two direct kernels.
+// Marching: its start, a step of a block, the same for every further block on
+// the CU, and the rate that memory bounds it by (TB/s).  Row streaming (waves of
+// `rows` rows by 64 lane vectors): its start, the time of a whole wave and of one
+// that the row's end cuts (ns, and per column of it), and how long one such wave
+// takes by itself (us), since the lanes beyond the row's end load cell by cell.
+// Fitted to both kernels' times on 91 grids of 2^20 to 2^27 cells, from 1 x
+// 1024^2 to 16384 x 8^2, so that the faster one is taken: within 9 % of it on each
+// (marching on all of them: up to 3.9 times, 1024 x 4 x 1024; row streaming: up
+// to 16 times, 1024 x 1024 x 4).
+struct Step3D {
+  int kind, r, rows;
+  double start, step, turn, rate;
+  double base, whole, cut, cut_column, alone, alone_column;
+};
+const Step3D kStep3D[] = {
+    {KIND_F32, 2, 2, 3.43, 0.849, 0.439, 4.04, 5.02, 1.71, 1.32, 0.00289, 6.21, 0.00253},
+    {KIND_F32, 3, 2, 3.20, 1.01, 0.895, 3.37, 5.73, 1.83, 2.47, 0.00403, 7.88, 0.0226},
+    {KIND_F32, 4, 4, 4.19, 1.21, 1.39, 3.49, 11.2, 5.33, 8.37, 0.0178, 8.49, 0.0652},
+    {KIND_F64, 2, 2, 5.63, 1.06, 0.889, 4.13, 2.82, 1.57, 1.17, 0.00553, 12.2, 0.000481},
+    {KIND_F64, 3, 2, 4.71, 1.19, 1.46, 4.03, 3.54, 1.68, 2.23, 0.00774, 16.5, 0.00463},
+    {KIND_F64, 4, 4, 2.26, 0.990, 1.04, 3.91, 7.52, 4.51, 8.08, 0.0231, 29.6, 0.0692},
+};
+
+bool march_faster(const s5d_plan* p, const MarchBlocks& b) {
+  for (const Step3D& s : kStep3D) {
+    if (s.kind != p->kind || s.r != p->d.radius) continue;
+    const double march = std::max(s.start + b.steps * (s.step + s.turn * (b.turns - 1.0)),
+                                  2.0 * static_cast<double>(p->bytes) / (s.rate * 1e6));
+    const int64_t seg = 64 * 16 / p->elem, cols = p->d.interior[2] % seg;
+    const double rows = static_cast<double>(p->d.interior[0] * ((p->d.interior[1] + s.rows - 1) / s.rows));
+    double row = 1e-3 * s.whole * rows * static_cast<double>(p->d.interior[2] / seg);
+    if (cols > 0) {
+      row += 1e-3 * rows * (s.cut + s.cut_column * static_cast<double>(cols));
+      row = std::max(row, s.alone + s.alone_column * static_cast<double>(cols));
+    }
+    return march < s.base + row;
+  }
+  return false;
+}
+
 // Direct kernels: one step per launch; the device coefficient table is made
 // here (the only device allocation of a plan).
 s5d_status plan_direct(s5d_plan* p, const s5d_tuning& req, int box, int r) {
@@ -408,16 +473,25 @@ s5d_status plan_direct(s5d_plan* p, const s5d_tuning& req, int box, int r) {
     if (!p->by_bt[1].launch) return fail(S5D_EUNSUPPORTED, "no direct 2D kernel for this stencil");
     p->tun.tile0 = p->by_bt[1].tile;
   } else {
-    // plain stars of radius 2..4 march once the grid has enough tiles to fill
-    // the machine (64^3, float32 radius 4: row streaming 20 us a step, marching
-    // 30; 143 x 151 x 140: 66 and 24) and its planes stay within a buffer
-    // descriptor's range; the float32 radius-2 star keeps row streaming where
-    // its rows are whole waves (512^3: 315 and 335, 420 x 512 x 483: 358 and 184)
+    // plain stars of radius 2..4 march from 2^20 cells on (64^3, float32 radius 4:
+    // row streaming 20 us a step, marching 30) where that is estimated to be
+    // faster and the planes stay within a buffer descriptor's range; the float32
+    // radius-2 star keeps row streaming where its rows are whole waves: on 19 such
+    // grids marching took 0.71 (300 x 300 x 512) to 1.95 times (1 x 1024^2) as long,
+    // at 512^3 344 us against 321, closer together than the estimate is exact
+    p->cus = query_device().cus;
     const double cells = static_cast<double>(p->d.interior[0]) * static_cast<double>(p->d.interior[1]) *
                          static_cast<double>(p->d.interior[2]);
     const double plane = static_cast<double>(p->padded[1]) * static_cast<double>(p->padded[2]) * p->elem;
     const bool whole_rows = p->kind == KIND_F32 && r == 2 && p->d.interior[2] % 256 == 0;
-    if (!box && cells >= 1 << 20 && plane < 2147483648.0 && !whole_rows) p->by_bt3[1] = s5d::march_kernel3d(p->kind, r);
+    if (!box && cells >= 1 << 20 && plane < 2147483648.0 && !whole_rows) {
+      const Kernel3D march = s5d::march_kernel3d(p->kind, r);
+      const MarchBlocks blocks = march.launch ? march_blocks(p, march) : MarchBlocks{};
+      if (march.launch && march_faster(p, blocks)) {
+        p->by_bt3[1] = march;
+        p->march_planes = blocks.planes;
+      }
+    }
     if (!p->by_bt3[1].launch) p->by_bt3[1] = s5d::direct_kernel3d(p->kind, r, box != 0);
     if (!p->by_bt3[1].launch) return fail(S5D_EUNSUPPORTED, "no direct 3D kernel for this stencil");
     p->tun.tile0 = p->by_bt3[1].m;
@@ -704,7 +778,7 @@ Round3D round3d(const s5d_plan* p, const void* src, void* dst, hipStream_t strea
   rd.I0 = static_cast<int32_t>(p->d.interior[0]);
   rd.I1 = static_cast<int32_t>(p->d.interior[1]);
   rd.I2 = static_cast<int32_t>(p->d.interior[2]);
-  rd.chunk = p->tun.stream_chunk;
+  rd.chunk = p->march_planes > 0 ? p->march_planes : p->tun.stream_chunk;
   rd.coeffs = p->coeffs.data();
   rd.stream = stream;
   return rd;
@@ -889,6 +963,7 @@ s5d_status s5d_plan_create(const s5d_desc* desc, const s5d_tuning* tuning, s5d_p
       p->by_bt3[b] = Kernel3D{};
     }
     p->direct = false;
+    p->march_planes = 0;
     p->chunk_auto = false;
     p->slots = 0;
     p->dcoef.reset();

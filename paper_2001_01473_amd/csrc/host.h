@@ -24,6 +24,7 @@ struct s5d_plan {
   int kind;                  // kernel kind: KIND_F32, KIND_F64 or KIND_F32_COMP
   int expr = 0;              // S5D_EXPR_*
   bool direct = false;       // direct kernels (one step per launch) instead of blocked ones
+  int march_planes = 0;      // marching kernel: planes per block
   bool chunk_auto = false;   // stream_chunk was chosen by the library (not asked for)
   int64_t slots = 0;         // 2D: resident waves of the plan's variant on the whole device
   bool tile_ok = false;      // 2D, blocking left to the library: small grids may run on resident tiles

@@ -212,11 +212,8 @@ int occupancy_march3d() {
   return nb;
 }
 
-// Geometry of a grid's launch; returns its workgroups (0: too large).  A block
-// of h planes takes h + 2r steps, rounded up to the unrolled 2r; the launch
-// lasts as long as the fullest CU (measured: 256^3 float32 radius 2, 240 blocks
-// of 32 planes 43 us, 480 of 16 46, 960 of 8 48, 330 of 24 58), less sharply so
-// from four blocks per CU on.
+// Geometry of a grid's launch in blocks of rd.chunk planes; returns its
+// workgroups (0: too large).
 template <typename T, int ACC, int R, int CPL, int M, int NW>
 int64_t march3d_args(March3DArgs& a, CoefPack<T, npts(3, R, false)>& cf, const Round3D& rd) {
   constexpr int C1 = NW * M - 2 * R, C2 = compute_width(64 * CPL, 1, R, sizeof(T));
@@ -228,20 +225,9 @@ int64_t march3d_args(March3DArgs& a, CoefPack<T, npts(3, R, false)>& cf, const R
   a.I2 = rd.I2;
   a.n1 = (rd.I1 + C1 - 1) / C1;
   a.n2 = (rd.I2 + C2 - 1) / C2;
-  const int64_t tiles = static_cast<int64_t>(a.n1) * a.n2;
-  double best = 1e300;
-  a.planes = rd.I0;
-  for (int64_t nb = 1; nb <= (rd.I0 + R - 1) / R; ++nb) {
-    const int64_t h = (rd.I0 + nb - 1) / nb;
-    const int64_t steps = (h + 2 * R + 2 * R - 1) / (2 * R) * (2 * R);
-    const double x = static_cast<double>(tiles * ((rd.I0 + h - 1) / h)) / 256.0;  // blocks per CU
-    const double cost = static_cast<double>(steps) * (x <= 1.0 ? 1.0 : (x < 4.0 ? __builtin_ceil(x) : x + 0.5));
-    if (cost < best) {
-      best = cost;
-      a.planes = static_cast<int32_t>(h);
-    }
-  }
-  const int64_t nblk = tiles * ((rd.I0 + a.planes - 1) / a.planes);
+  a.planes = rd.chunk;
+  if (a.planes < 1) return 0;
+  const int64_t nblk = static_cast<int64_t>(a.n1) * a.n2 * ((rd.I0 + a.planes - 1) / a.planes);
   return nblk > INT32_MAX ? 0 : nblk;
 }
 

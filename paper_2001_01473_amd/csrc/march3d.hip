@@ -9,7 +9,7 @@ template <typename T, int R, int CPL, int M, int NW>
 Kernel3D make() {
   return Kernel3D{&launch_march3d<T, 0, R, CPL, M, NW>,
                   &occupancy_march3d<T, 0, R, CPL, M, NW>,
-                  0,
+                  CPL,
                   NW * M,
                   1,
                   1,
