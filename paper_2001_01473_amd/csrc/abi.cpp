@@ -240,38 +240,28 @@ int one_turn(int64_t I0, int64_t ntiles, int64_t slots, int h, int warmup) {
 // A whole sweep as (n_full rounds of bt) followed by up to three shorter
 // rounds; the total round count has the parity of T, so the result lands in
 // buffer T % 2 (AN5D "Host Code").
-struct RoundSchedule {
-  int64_t n_full = 0;
-  int bt = 1;
-  int tail[3] = {0, 0, 0};
-  int n_tail = 0;
-  int64_t total() const { return n_full + n_tail; }
-};
-
-RoundSchedule schedule_rounds(int64_t T, int bt) {
-  RoundSchedule s;
-  s.bt = bt;
+s5d::Rounds schedule_rounds(int64_t T, int bt) {
+  s5d::Rounds s;
   if (T <= 0) return s;
   const int64_t n = (T + bt - 1) / bt;
   const int last = static_cast<int>(T - (n - 1) * bt);
   if ((n % 2) == (T % 2)) {
     if (last == bt) {
-      s.n_full = n;
+      s.add(n, bt);
     } else {
-      s.n_full = n - 1;
-      s.tail[s.n_tail++] = last;
+      s.add(n - 1, bt);
+      s.add(1, last);
     }
   } else if (last >= 2) {
-    s.n_full = n - 1;
-    s.tail[s.n_tail++] = last - 1;
-    s.tail[s.n_tail++] = 1;
+    s.add(n - 1, bt);
+    s.add(1, last - 1);
+    s.add(1, 1);
   } else {
     // last == 1 and n >= 2 (n == 1 would mean T == 1, which matches parity);
     // a mismatch needs bt >= 2, so the round before can give up one step.
-    s.n_full = n - 2;
-    s.tail[s.n_tail++] = bt - 1;
-    s.tail[s.n_tail++] = 1;
-    s.tail[s.n_tail++] = 1;
+    s.add(n - 2, bt);
+    s.add(1, bt - 1);
+    s.add(2, 1);
   }
   return s;
 }
@@ -386,9 +376,9 @@ bool choose_depth3(const s5d_plan* p, int box, int r, Default3D* out) {
       const double us = x->start + (h + 2.0 * bt * r) * turns3(n, x->alone, x->shared);
       return std::max(us, 2.0 * static_cast<double>(p->bytes) / (2 * p->bytes > 256e6 ? 4e6 : 9e6));
     };
-    const RoundSchedule s = schedule_rounds(p->d.steps, l.bt);
-    double us = s.n_full > 0 ? static_cast<double>(s.n_full) * launch_us(s.bt) : 0.0;
-    for (int k = 0; k < s.n_tail; ++k) us += launch_us(s.tail[k]);
+    const s5d::Rounds s = schedule_rounds(p->d.steps, l.bt);
+    double us = 0;
+    for (int k = 0; k < s.n_runs; ++k) us += static_cast<double>(s.runs[k].n) * launch_us(s.runs[k].bt);
     if (us < best) {
       best = us;
       *out = {l.bt, l.m};
@@ -650,14 +640,7 @@ s5d_status plan_3d(s5d_plan* p, const s5d_tuning& req, int box, int r) {
 
 namespace s5d {
 
-std::vector<int> plan_rounds(const s5d_plan* p) {
-  const RoundSchedule rs = schedule_rounds(p->d.steps, p->tun.bt);
-  std::vector<int> out;
-  out.reserve(static_cast<size_t>(rs.total()));
-  for (int64_t i = 0; i < rs.n_full; ++i) out.push_back(rs.bt);
-  for (int i = 0; i < rs.n_tail; ++i) out.push_back(rs.tail[i]);
-  return out;
-}
+Rounds plan_rounds(const s5d_plan* p) { return schedule_rounds(p->d.steps, p->tun.bt); }
 
 namespace {
 
@@ -739,9 +722,9 @@ Rounds tile_rounds(const s5d_plan* p, double share, double* us) {
       }
     }
   }
-  out.bt.reserve(static_cast<size_t>(n_best));
   const int64_t q = T / n_best, rem = T % n_best;
-  for (int64_t i = 0; i < n_best; ++i) out.bt.push_back(static_cast<int>(q + (i < rem ? 1 : 0)));
+  out.add(rem, static_cast<int>(q + 1));
+  out.add(n_best - rem, static_cast<int>(q));
   return out;
 }
 
@@ -749,11 +732,8 @@ double own_rounds_us(const s5d_plan* p, double share) { return p->tile_ok ? own_
 
 Rounds choose_rounds(const s5d_plan* p, double share) {
   double us = 0;
-  Rounds out = tile_rounds(p, share, &us);
-  if (out.tile && us < 0.95 * own_us(p, share)) return out;
-  out.tile = nullptr;
-  out.bt = plan_rounds(p);
-  return out;
+  const Rounds out = tile_rounds(p, share, &us);
+  return out.tile && us < 0.95 * own_us(p, share) ? out : plan_rounds(p);
 }
 
 namespace {
@@ -1026,6 +1006,7 @@ s5d_status s5d_plan_create(const s5d_desc* desc, const s5d_tuning* tuning, s5d_p
     delete p;
     return st;
   }
+  p->rounds = s5d::choose_rounds(p, 1.0);
   *out = p;
   return S5D_OK;
 }
@@ -1068,11 +1049,13 @@ s5d_status s5d_run_fields(const s5d_plan* plan, void* buf0, void* buf1, const vo
   hipError_t e = s5d::launch_boundary_copy(plan, buf0, buf1, st);
   if (e != hipSuccess) return device_fail(e, "boundary copy launch");
   void* bufs[2] = {buf0, buf1};
-  const s5d::Rounds rounds = s5d::choose_rounds(plan, 1.0);
-  for (size_t k = 0; k < rounds.bt.size(); ++k) {
-    e = s5d::launch_round(plan, rounds.tile, rounds.bt[k], bufs[k % 2], bufs[(k + 1) % 2], st, fields);
-    if (e != hipSuccess) return device_fail(e, "sweep launch");
-  }
+  const s5d::Rounds& rounds = plan->rounds;
+  int64_t k = 0;
+  for (int i = 0; i < rounds.n_runs; ++i)
+    for (int64_t j = 0; j < rounds.runs[i].n; ++j, ++k) {
+      e = s5d::launch_round(plan, rounds.tile, rounds.runs[i].bt, bufs[k % 2], bufs[(k + 1) % 2], st, fields);
+      if (e != hipSuccess) return device_fail(e, "sweep launch");
+    }
   return S5D_OK;
 }
 
@@ -1137,11 +1120,11 @@ s5d_status s5d_error_norms_noalloc(const void* got, int32_t got_dtype, const voi
   return S5D_OK;
 }
 
-int32_t s5d_internal_rounds(const s5d_plan* plan, double share, int32_t* tile_rows, int32_t* tile_cols) {
+int64_t s5d_internal_rounds(const s5d_plan* plan, double share, int32_t* tile_rows, int32_t* tile_cols) {
   const s5d::Rounds r = s5d::choose_rounds(plan, share);
   *tile_rows = r.tile ? r.tile->rows : 0;
   *tile_cols = r.tile ? r.tile->cols : 0;
-  return static_cast<int32_t>(r.bt.size());
+  return r.size();
 }
 
 }  // extern "C"

@@ -265,7 +265,7 @@ namespace s5d {
 // Persistent mode: group the grids by stencil family, lay out each family's
 // round table, work items and control block in `blob`, and size its launch.
 s5d_status build_persistent(s5d_batch* b, const s5d_plan* const* plans, void* const* buf0, void* const* buf1,
-                            int32_t n, const std::vector<std::vector<int>>& rounds, const std::vector<int>& chunks,
+                            int32_t n, const std::vector<Rounds>& rounds, const std::vector<int>& chunks,
                             const std::vector<double>& work, std::vector<unsigned char>& blob) {
   // family of every grid with work
   std::vector<int> fam(static_cast<size_t>(n), -1);
@@ -275,7 +275,7 @@ s5d_status build_persistent(s5d_batch* b, const s5d_plan* const* plans, void* co
     const int box = p->d.shape == S5D_BOX ? 1 : 0;
     if (p->d.ndim != 2 || p->direct)
       return fail(S5D_EUNSUPPORTED, "grid " + std::to_string(g) + ": persistent batches run 2D blocked plans only");
-    const int bt_max = *std::max_element(rounds[g].begin(), rounds[g].end());
+    const int bt_max = rounds[g].deepest();
     for (int i = 0; i < kRegistryP2DSize; ++i) {
       const EntryP2D& e = kRegistryP2D[i];
       if (e.dtype == p->kind && e.expr == p->expr && e.box == box && e.r == p->d.radius &&
@@ -321,7 +321,7 @@ s5d_status build_persistent(s5d_batch* b, const s5d_plan* const* plans, void* co
     for (size_t j = 0; j < members.size(); ++j) {
       const int32_t g = members[j];
       void* bufs[2] = {buf0[g], buf1[g]};
-      for (size_t k = 0; k < rounds[g].size(); ++k) {
+      for (int64_t k = 0; k < rounds[g].size(); ++k) {
         const int nb = fill_persist_round(plans[g], f.k, rounds[g][k], bufs[k % 2], bufs[(k + 1) % 2], scratch,
                                           pchunk[g], 0, 0);
         if (nb <= 0) return fail(S5D_EUNSUPPORTED, "grid " + std::to_string(g) + ": round does not fit a launch");
@@ -401,8 +401,8 @@ s5d_status s5d_batch_create(const s5d_plan* const* plans, void* const* buf0, voi
   if (!b) return fail(S5D_ENOMEM, "batch allocation failed");
   b->graph = (flags & S5D_BATCH_GRAPH) != 0;
   b->persistent = (flags & S5D_BATCH_PERSISTENT) != 0;
-  std::vector<std::vector<int>> rounds(static_cast<size_t>(n));
-  size_t kmax = 0;
+  std::vector<s5d::Rounds> rounds(static_cast<size_t>(n));
+  int64_t kmax = 0;
   try {
     std::vector<s5d::HaloItem> halos;
     b->result_index.resize(static_cast<size_t>(n));
@@ -443,7 +443,6 @@ s5d_status s5d_batch_create(const s5d_plan* const* plans, void* const* buf0, voi
     // slowest grid (24 float32 stars of 256 to 2048 cells a side: 6.4 ms on
     // their own kernels, 6.6 mixed by each grid's own estimate).
     // Plans whose own kernels cannot be batched stay refused.
-    std::vector<const s5d::TileKernel2D*> tiles(static_cast<size_t>(n), nullptr);
     if (!b->persistent && total_work > 0) {
       std::vector<s5d::Rounds> on_tiles(static_cast<size_t>(n));
       double tile_us = 0, own_us = 0;
@@ -457,13 +456,10 @@ s5d_status s5d_batch_create(const s5d_plan* const* plans, void* const* buf0, voi
       }
       if (tile_us < own_us)
         for (int32_t g = 0; g < n; ++g)
-          if (on_tiles[g].tile) {
-            rounds[g] = std::move(on_tiles[g].bt);
-            tiles[g] = on_tiles[g].tile;
-          }
+          if (on_tiles[g].tile) rounds[g] = on_tiles[g];
     }
     for (int32_t g = 0; g < n; ++g)
-      if (!rounds[g].empty() && total_work > 0 && !tiles[g])
+      if (!rounds[g].empty() && total_work > 0 && !rounds[g].tile)
         chunks[g] = s5d::shared_chunk(plans[g], plans[g]->tun.bt, work[g] / total_work);
     kmax = 0;
     for (int32_t g = 0; g < n; ++g) kmax = std::max(kmax, rounds[g].size());
@@ -481,15 +477,16 @@ s5d_status s5d_batch_create(const s5d_plan* const* plans, void* const* buf0, voi
       }
       kmax = 0;  // no per-round-index steps
     }
-    b->steps.resize(kmax);
-    for (size_t k = 0; k < kmax; ++k) {
+    b->steps.resize(static_cast<size_t>(kmax));
+    for (int64_t k = 0; k < kmax; ++k) {
       std::vector<s5d::RoundItem> items;
       for (int32_t g = 0; g < n; ++g) {
         if (k >= rounds[g].size()) continue;
         void* bufs[2] = {buf0[g], buf1[g]};
-        items.push_back(s5d::RoundItem{plans[g], tiles[g], rounds[g][k], bufs[k % 2], bufs[(k + 1) % 2], chunks[g]});
+        items.push_back(
+            s5d::RoundItem{plans[g], rounds[g].tile, rounds[g][k], bufs[k % 2], bufs[(k + 1) % 2], chunks[g]});
       }
-      const s5d_status st = s5d::build_step(items, blob, b->steps[k]);
+      const s5d_status st = s5d::build_step(items, blob, b->steps[static_cast<size_t>(k)]);
       if (st != S5D_OK) {
         release(b);
         return st;

@@ -14,6 +14,45 @@
 #include "stencil5d.h"
 #include "tile.h"
 
+namespace s5d {
+
+// The rounds of a sweep in launch order, as runs of equal fused depth (none for
+// T = 0: however many steps, at most four runs), and, if they run on resident
+// tiles, that kernel (else null: the plan's own kernels).  Round k reads buffer
+// k % 2 and writes buffer (k + 1) % 2; the number of rounds has the parity of T,
+// so the result is in buffer T % 2.
+struct Rounds {
+  struct Run {
+    int64_t n;
+    int bt;
+  };
+  Run runs[4] = {};
+  int n_runs = 0;
+  const TileKernel2D* tile = nullptr;
+
+  void add(int64_t n, int bt) {
+    if (n > 0) runs[n_runs++] = Run{n, bt};
+  }
+  int64_t size() const {
+    int64_t n = 0;
+    for (int i = 0; i < n_runs; ++i) n += runs[i].n;
+    return n;
+  }
+  bool empty() const { return n_runs == 0; }
+  int operator[](int64_t k) const {  // depth of round k
+    int i = 0;
+    while (i + 1 < n_runs && k >= runs[i].n) k -= runs[i++].n;
+    return runs[i].bt;
+  }
+  int deepest() const {
+    int bt = 0;
+    for (int i = 0; i < n_runs; ++i) bt = runs[i].bt > bt ? runs[i].bt : bt;
+    return bt;
+  }
+};
+
+}  // namespace s5d
+
 struct s5d_plan {
   s5d_desc d;
   std::vector<double> coeffs;
@@ -29,6 +68,7 @@ struct s5d_plan {
   int64_t slots = 0;         // 2D: resident waves of the plan's variant on the whole device
   bool tile_ok = false;      // 2D, blocking left to the library: small grids may run on resident tiles
   int cus = 256;             // compute units of the device
+  s5d::Rounds rounds;        // what s5d_run launches, chosen once when the plan is made
   s5d::Kernel2D by_bt[16];   // 2D: index bt -> kernel for a round of bt steps (same tile)
   s5d::Kernel3D by_bt3[16];  // 3D: likewise
   // device copy of the coefficients in the working type (direct kernels);
@@ -43,17 +83,8 @@ s5d_status fail(s5d_status st, const std::string& msg);
 s5d_status device_fail(hipError_t e, const char* what);
 void clear_error();
 
-// The rounds of a sweep: the fused depth of each in launch order (empty for T
-// = 0) and, if they run on resident tiles, that kernel (else null: the plan's
-// own kernels).  Round k reads buffer k % 2 and writes buffer (k + 1) % 2; the
-// number of rounds has the parity of T, so the result is in buffer T % 2.
-struct Rounds {
-  std::vector<int> bt;
-  const TileKernel2D* tile = nullptr;
-};
-
 // The rounds of a plan's sweep on its own kernels.
-std::vector<int> plan_rounds(const s5d_plan* p);
+Rounds plan_rounds(const s5d_plan* p);
 
 // The rounds the library gives a plan that gets about `share` (0 < share <= 1)
 // of the machine: on resident tiles where the plan leaves the choice to the
@@ -115,4 +146,4 @@ void load_default_tuning();
 
 // For the tests, not part of the ABI: the rounds of a plan's sweep, and the
 // resident tile they run on (0 x 0: the plan's own kernels).
-extern "C" int32_t s5d_internal_rounds(const s5d_plan* plan, double share, int32_t* tile_rows, int32_t* tile_cols);
+extern "C" int64_t s5d_internal_rounds(const s5d_plan* plan, double share, int32_t* tile_rows, int32_t* tile_cols);

@@ -47,9 +47,8 @@ struct Request {
   int32_t state = S5D_REQ_QUEUED;
   s5d_status status = S5D_OK;    // why a FAILED request failed
   double t_arrival = 0, t_admit = -1, t_done = -1;
-  std::vector<int> rounds;
-  const s5d::TileKernel2D* tile = nullptr;  // kernel of the rounds, if they run on resident tiles
-  size_t next = 0;
+  s5d::Rounds rounds;
+  int64_t next = 0;
   void* buf[2] = {nullptr, nullptr};
   int64_t bytes2 = 0;  // both buffers
   int64_t updates = 0;
@@ -221,9 +220,7 @@ s5d_status admit(s5d_server* s, Request* r) {
   for (const Request* q : s->running) all += static_cast<double>(q->updates);
   for (const Request* q : s->queue) all += static_cast<double>(q->updates);
   all += static_cast<double>(r->updates);
-  const s5d::Rounds rounds = s5d::choose_rounds(&r->plan, all > 0 ? static_cast<double>(r->updates) / all : 1.0);
-  r->rounds = rounds.bt;
-  r->tile = rounds.tile;
+  r->rounds = s5d::choose_rounds(&r->plan, all > 0 ? static_cast<double>(r->updates) / all : 1.0);
   if (!r->rounds.empty()) {
     e = s5d::launch_boundary_copy(&r->plan, r->buf[0], r->buf[1], s->stream);
     if (e != hipSuccess) return device_fail(e, "boundary copy launch");
@@ -293,12 +290,10 @@ double percentile(std::vector<double> v, double q) {
 // Can every round of this plan go into a batched launch?  (Checked at
 // submission, so that a tick never meets a request it cannot launch.)
 s5d_status check_batchable(const s5d_plan* p) {
-  const std::vector<int> rounds = s5d::plan_rounds(p);
-  std::vector<int> seen;
+  const s5d::Rounds rounds = s5d::plan_rounds(p);
   static char dummy[2][16];
-  for (int bt : rounds) {
-    if (std::find(seen.begin(), seen.end(), bt) != seen.end()) continue;
-    seen.push_back(bt);
+  for (int i = 0; i < rounds.n_runs; ++i) {
+    const int bt = rounds.runs[i].bt;
     const s5d::BatchHooks h = s5d::batch_hooks(p, nullptr, bt);
     if (!h.launch || h.item_bytes <= 0) return fail(S5D_EUNSUPPORTED, "kernel variant without a batched entry point");
     std::vector<unsigned char> item(static_cast<size_t>(h.item_bytes) + 16);
@@ -470,7 +465,7 @@ s5d_status s5d_server_tick(s5d_server* s, int32_t* n_running, int32_t* n_queued)
                       ? s->cfg.rounds_per_tick
                       : std::min(kMaxRoundsPerTick, std::max(1, (kTargetLaunches + n - 1) / n));
     std::vector<Request*> act = s->running;
-    std::vector<size_t> nx(act.size());
+    std::vector<int64_t> nx(act.size());
     for (size_t i = 0; i < act.size(); ++i) nx[i] = act[i]->next;
     std::vector<unsigned char> blob;
     std::vector<std::vector<s5d::GroupLaunch>> steps;
@@ -492,10 +487,10 @@ s5d_status s5d_server_tick(s5d_server* s, int32_t* n_running, int32_t* n_queued)
         for (size_t i = 0; i < act.size(); ++i) {
           Request* r = act[i];
           if (nx[i] >= r->rounds.size()) continue;
-          const size_t k = nx[i]++;
+          const int64_t k = nx[i]++;
           const int bt = r->rounds[k];
-          const int chunk = r->tile ? 0 : s5d::shared_chunk(&r->plan, bt, bt * cells_of(r) / step_work);
-          items.push_back(s5d::RoundItem{&r->plan, r->tile, bt, r->buf[k % 2], r->buf[(k + 1) % 2], chunk});
+          const int chunk = r->rounds.tile ? 0 : s5d::shared_chunk(&r->plan, bt, bt * cells_of(r) / step_work);
+          items.push_back(s5d::RoundItem{&r->plan, r->rounds.tile, bt, r->buf[k % 2], r->buf[(k + 1) % 2], chunk});
           in_step.back().push_back(i);
           if (nx[i] == r->rounds.size()) fin_after.back().push_back(r);
         }
@@ -595,7 +590,7 @@ s5d_status s5d_server_request(const s5d_server* s, int64_t id, s5d_request_info*
   info->t_arrival = r->t_arrival;
   info->t_admit = r->t_admit;
   info->t_done = r->t_done;
-  info->rounds_done = static_cast<int64_t>(r->next);
+  info->rounds_done = r->next;
   info->init_in_use = (r->state == S5D_REQ_QUEUED || !init_released(s, r)) ? 1 : 0;
   return S5D_OK;
 }

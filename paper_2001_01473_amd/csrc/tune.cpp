@@ -223,17 +223,11 @@ s5d_status model_plan(const s5d_plan* p, s5d_model* out) {
   const Rates rt = device_rates();
   double t_alu = 0, t_hbm = 0, t_lds = 0, total = 0, ops = 0, bytes = 0, eff_main = 1;
   int64_t wgs_main = 0;
-  const std::vector<int> rounds = plan_rounds(p);
-  std::map<int, RoundModel> cache;
-  for (size_t k = 0; k < rounds.size(); ++k) {
-    const int bt = rounds[k];
-    auto it = cache.find(bt);
-    if (it == cache.end())
-      it = cache
-               .emplace(bt, p->direct ? model_round_direct(p)
-                                      : (p->d.ndim == 3 ? model_round3d(p, bt) : model_round2d(p, bt)))
-               .first;
-    const RoundModel& m = it->second;
+  const Rounds rounds = plan_rounds(p);
+  for (int k = 0; k < rounds.n_runs; ++k) {
+    const int bt = rounds.runs[k].bt;
+    const double n = static_cast<double>(rounds.runs[k].n);
+    const RoundModel m = p->direct ? model_round_direct(p) : (p->d.ndim == 3 ? model_round3d(p, bt) : model_round2d(p, bt));
     const double valu = rt.valu;  // float32 (unpacked) and float64 issue at one rate
     const double ta = m.ops / valu, tg = m.gm / rt.hbm, tl = m.lds / rt.lds;
     // slot efficiency: with fewer workgroups than resident slots the machine
@@ -242,12 +236,12 @@ s5d_status model_plan(const s5d_plan* p, s5d_model* out) {
     const double slots = static_cast<double>(rt.cus) * m.wg_per_cu;
     const double frac = slots / static_cast<double>(std::max<int64_t>(m.wgs, 1));
     const double fill = 1.0 / (std::max(1.0, frac) + kTail * std::min(1.0, frac));
-    total += std::max(ta, std::max(tg, tl)) / fill;
-    t_alu += ta;
-    t_hbm += tg;
-    t_lds += tl;
-    ops += m.ops;
-    bytes += m.gm;
+    total += n * (std::max(ta, std::max(tg, tl)) / fill);
+    t_alu += n * ta;
+    t_hbm += n * tg;
+    t_lds += n * tl;
+    ops += n * m.ops;
+    bytes += n * m.gm;
     if (k == 0) {
       eff_main = fill;
       wgs_main = m.wgs;
@@ -357,7 +351,7 @@ s5d_status library_choice(const s5d_desc& d, const s5d_tuning* tuning, Choice* c
   const s5d_status rc = s5d_plan_create(&d, tuning, &p);
   if (rc != S5D_OK) return rc;
   c->tun = p->tun;
-  c->tiles = s5d::choose_rounds(p, 1.0).tile != nullptr;
+  c->tiles = p->rounds.tile != nullptr;
   c->direct = p->direct;
   c->bytes = p->bytes;
   s5d_plan_destroy(p);
