@@ -319,16 +319,21 @@ double turns3(int64_t n, double alone, double shared) {
 // divisor, 400 x 300 x 200: 66 us at h = 8, 81 at 34).  The 7-point stars take 6
 // planes (512^3, float32 / float64: h = 6 293 / 493 us, h = 8 321 / 522), float64
 // 4 on grids that the caches hold in good part (400 x 300 x 200: h = 4 / 6 / 8 70 /
-// 77 / 79 us).  So it is for the float32 7-point star, the lightest, at every depth
-// once both buffers pass 1 GB (b_T = 3, 60 steps: 512^3 h = 27 6.55 ms, 103 6.72;
-// 420 x 512 x 483 h = 27 5.44, 84 5.13).
-int choose_chunk3(const s5d_plan* p, int rows, int cols, int m, int bt, int box, int r) {
+// 77 / 79 us).  So it is for the float32 7-point star, the lightest, at the deeper
+// rounds too once a buffer passes 450 MB: 20 planes.  Measured on 24 grids of 110
+// MB to 1.8 GB a buffer, time over the best of 13 block lengths, 20 planes / whole
+// turns: 350^3 (174 MB) 1.03 / 1.00, 420 x 512 x 483 (421) 1.03 / 1.00, 480^3 (448)
+// 1.05 / 1.05, 512 x 470 x 480 (468) 1.01 / 1.05, 512^3 (543) 1.00 / 1.04; above,
+// to 768^3, 20 planes 1.00 to 1.06 (128 x 1200^2 1.09).  `resident`: workgroups of
+// the kernel that fit a CU, at most two.
+int choose_chunk3(const s5d_plan* p, int rows, int cols, int m, int bt, int box, int r, int resident = 2) {
   const int64_t I0 = p->d.interior[0], ntiles = tiles3d(p, rows, cols, bt, r), cus = p->cus;
   if (bt == 1 && ntiles * (I0 / 8) > 2 * cus) {
-    if (box || r > 1) return choose_chunk(I0, ntiles, 2 * cus, bt, r);
+    if (box || r > 1) return choose_chunk(I0, ntiles, resident * cus, bt, r);
     return p->kind == KIND_F64 && 2 * p->bytes <= 512e6 ? 4 : 6;
   }
-  if (p->kind == KIND_F32 && !box && r == 1 && p->bytes > 500000000) return choose_chunk(I0, ntiles, 2 * cus, bt, r);
+  if (p->kind == KIND_F32 && !box && r == 1 && bt > 1 && p->bytes > 450000000)
+    return static_cast<int>(std::min<int64_t>(I0, 20));
   const Launch3D* l = find_launch3(p->kind, box, r, m, bt);
   const double alone = l ? std::max(1.0, l->alone / l->shared) : 1.0;
   int64_t best_h = I0;
@@ -623,7 +628,8 @@ s5d_status plan_3d(s5d_plan* p, const s5d_tuning& req, int box, int r) {
   const int B1 = fam->m * fam->nw, B2 = 64 * fam->cpl;
   int chunk = req.stream_chunk;
   if (chunk == 0) {
-    chunk = choose_chunk3(p, B1, B2, fam->m, bt, box, r);
+    const int occ = dev.ok ? p->by_bt3[bt].occupancy() : 0;
+    chunk = choose_chunk3(p, B1, B2, fam->m, bt, box, r, occ == 1 ? 1 : 2);
     p->chunk_auto = true;
   }
   if (chunk < 1) return fail(S5D_EINVAL, "stream_chunk must be >= 1");
