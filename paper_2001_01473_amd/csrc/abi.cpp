@@ -569,7 +569,13 @@ s5d_status plan_2d(s5d_plan* p, const s5d_tuning& req, int box, int r) {
   if (chunk == 0) {
     const int64_t C = s5d::compute_width(64 * cpl, bt, r, p->elem);
     const int64_t ntiles = (d.interior[1] + C - 1) / C;
-    chunk = choose_chunk(d.interior[0], ntiles, p->slots, bt, r);
+    // a box of radius 3 or 4 issues 49 or 81 FMAs a cell: one wave keeps its SIMD
+    // busy, and further resident ones only share it (two rounds at the block length
+    // for one wave a SIMD / for all resident ones: float32 radius 3, b_T = 2, 3000 x
+    // 4100 h = 30 151 us / 17 205, 16384^2 128 1833 / 77 1929; float64 radius 4, b_T = 1,
+    // 3000 x 4100 24 273 / 15 316, 16384^2 113 2790 / 77 3007)
+    const int64_t slots = box && r >= 3 ? int64_t{4} * p->cus : p->slots;
+    chunk = choose_chunk(d.interior[0], ntiles, slots, bt, r);
     if (ex == s5d::EXPR_VARCOEF && p->slots <= int64_t{4} * p->cus)
       chunk = one_turn(d.interior[0], ntiles, p->slots, chunk, 2 * bt * r);
     p->chunk_auto = true;
