@@ -52,6 +52,7 @@ struct Request {
   void* buf[2] = {nullptr, nullptr};
   int64_t bytes2 = 0;  // both buffers
   int64_t updates = 0;
+  bool held = false;  // counted in the server's work (queued or running)
 };
 
 double cells_of(const Request* r) { return static_cast<double>(r->plan.bytes / r->plan.elem); }
@@ -85,6 +86,7 @@ struct s5d_server {
   Slot slots[kSlots];
   int64_t next_id = 1;
   int64_t used = 0, peak = 0;
+  int64_t work = 0;  // cell updates of the queued and running requests
   int64_t ticks = 0, launches = 0, done = 0, failed = 0, updates_done = 0;
   int64_t admissions = 0, work_ticks = 0;  // counters of the fault-injection knobs
   double first_arrival = -1, last_done = -1;
@@ -108,6 +110,12 @@ s5d_status take_event(s5d_server* s, hipEvent_t* ev) {
   }
   const hipError_t e = hipEventCreate(ev);
   return e == hipSuccess ? S5D_OK : device_fail(e, "hipEventCreate");
+}
+
+// The request leaves the queue or the running ones.
+void leave(s5d_server* s, Request* r) {
+  if (r->held) s->work -= r->updates;
+  r->held = false;
 }
 
 void release_buffers(s5d_server* s, Request* r) {
@@ -134,6 +142,7 @@ bool init_released(const s5d_server* cs, Request* r) {
 
 // A request that will not run (any more): FAILED, memory returned.
 void fail_request(s5d_server* s, Request* r, s5d_status why) {
+  leave(s, r);
   release_buffers(s, r);
   r->state = S5D_REQ_FAILED;
   r->status = why;
@@ -176,8 +185,10 @@ s5d_status record_finish(s5d_server* s, const std::vector<Request*>& reqs) {
     s->event_pool.push_back(ev);
     return device_fail(e, "hipEventRecord");
   }
-  for (Request* r : reqs)
+  for (Request* r : reqs) {
+    leave(s, r);
     if (!r->keep) release_buffers(s, r);
+  }
   s->finishing.push_back(Finishing{ev, reqs});
   return S5D_OK;
 }
@@ -215,12 +226,9 @@ s5d_status admit(s5d_server* s, Request* r) {
   }
   r->init_ev = ev;
   r->init = nullptr;
-  // the request's share of the work the server holds
-  double all = 0;
-  for (const Request* q : s->running) all += static_cast<double>(q->updates);
-  for (const Request* q : s->queue) all += static_cast<double>(q->updates);
-  all += static_cast<double>(r->updates);
-  r->rounds = s5d::choose_rounds(&r->plan, all > 0 ? static_cast<double>(r->updates) / all : 1.0);
+  // its share of the work the server holds, itself included
+  r->rounds = s5d::choose_rounds(
+      &r->plan, s->work > 0 ? static_cast<double>(r->updates) / static_cast<double>(s->work) : 1.0);
   if (!r->rounds.empty()) {
     e = s5d::launch_boundary_copy(&r->plan, r->buf[0], r->buf[1], s->stream);
     if (e != hipSuccess) return device_fail(e, "boundary copy launch");
@@ -391,6 +399,8 @@ s5d_status s5d_server_submit(s5d_server* s, const s5d_plan* plan, const void* in
   Request* raw = r.get();
   s->reqs[raw->id] = std::move(r);
   s->queue.push_back(raw);
+  raw->held = true;
+  s->work += raw->updates;
   if (id) *id = raw->id;
   return S5D_OK;
 }
