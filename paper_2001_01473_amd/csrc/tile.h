@@ -13,7 +13,7 @@ namespace s5d {
 struct TileKernel2D {
   hipError_t (*launch)(const Round2D&, int bt);
   int (*fill_item)(void* item, const Round2D&, int bt);  // returns the grid's workgroups
-  LaunchBatchFn launch_batch;
+  LaunchBatchFn launch_batch;                            // null (and fill_item): not batched
   int item_bytes;
   int rows, cols;   // tile, overlap included
   int step_clocks;  // clocks of vector issue one workgroup's step takes of a CU (an estimate)

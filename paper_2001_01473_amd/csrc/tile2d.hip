@@ -23,13 +23,17 @@ TileKernel2D make() {
   // the wide float64 tiles of radius >= 2 take so many registers that a CU
   // holds one workgroup: nothing overlaps its exchange (measured a quarter)
   constexpr int clocks = instr * NW * (words == 2 && R >= 2 && CPL == 2 ? 5 : 4) / 4;
-  return TileKernel2D{&launch_tile2d<T, ACC, EXPR, R, BOX, CPL, M, NW>,
-                      &fill_tile2d<T, EXPR, R, BOX, CPL, M, NW>,
-                      &launch_tile2d_batch<T, ACC, EXPR, R, BOX, CPL, M, NW>,
-                      static_cast<int>(sizeof(TileItem2D<T, ncoef(2, R, BOX, EXPR)>)),
-                      NW * M,
-                      64 * CPL,
-                      clocks};
+  // gradient2d is not batched: its streaming kernels have no batched entry point
+  if constexpr (EXPR == EXPR_GRADIENT)
+    return TileKernel2D{&launch_tile2d<T, ACC, EXPR, R, BOX, CPL, M, NW>, nullptr, nullptr, 0, NW * M, 64 * CPL, clocks};
+  else
+    return TileKernel2D{&launch_tile2d<T, ACC, EXPR, R, BOX, CPL, M, NW>,
+                        &fill_tile2d<T, EXPR, R, BOX, CPL, M, NW>,
+                        &launch_tile2d_batch<T, ACC, EXPR, R, BOX, CPL, M, NW>,
+                        static_cast<int>(sizeof(TileItem2D<T, ncoef(2, R, BOX, EXPR)>)),
+                        NW * M,
+                        64 * CPL,
+                        clocks};
 }
 
 template <typename T, int ACC, int EXPR, int R, bool BOX>
