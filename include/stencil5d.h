@@ -137,8 +137,9 @@ typedef struct s5d_tuning {
 #define S5D_KERNEL_BLOCKED 1 /* b_T fused steps per launch (AN5D "Execution Model") */
 #define S5D_KERNEL_DIRECT 2  /* one step per launch, every radius 1..4 and shape: 2D stars
                                 and boxes of radius <= 2 and 3D stars stream whole
-                                rows (large plain 3D stars of radius >= 2 march
-                                along axis 0), the others work from an LDS-staged
+                                rows (plain 3D stars of radius >= 2 march along
+                                axis 0 where that is estimated to be faster), the
+                                others work from an LDS-staged
                                 tile (the plan's bt is 1) */
 
 typedef struct s5d_plan s5d_plan; /* opaque; immutable once created */

@@ -252,7 +252,8 @@ def autotune(*, ndim, radius, box, dtype, interior, steps, coeffs=None, accum="p
              stream=None, expr="linear"):
     """Model-ranked, GPU-measured choice of the blocking for this problem
     (``s5d_autotune``); returns (tuning dict, report dict).  The choice is
-    cached for later plans of the same stencil and extent bucket."""
+    cached for later plans of the same stencil and extent bucket, unless what a
+    plan without tuning runs (on resident tiles, where it does) is as fast."""
     lib = _lib.load()
     desc, keep = _lib.make_desc(ndim, radius, box, _dtype_code(dtype), _accum_code(accum),
                                 interior, steps, coeffs, _expr_code(expr))

@@ -65,7 +65,7 @@ EXPR_TAG = {0: "", 1: "div_", 2: "grad_", 3: "varc_"}
 # and the variable-coefficient stars and 3x3 box.
 EXPR_2D = [(1, 0, 1), (1, 0, 2), (1, 1, 1), (2, 0, 1), (3, 0, 1), (3, 0, 2), (3, 1, 1)]
 # Deepest fused depth compiled per expression (window kernels keep 2r+1 rows
-# per level; per-cell weights add n loads per cell and level).
+# per level; per-cell weights also (b_T - 1) r + 1 rows of n weights in LDS).
 MAX_BT_EXPR = {1: 10, 2: 10, 3: 4}
 
 

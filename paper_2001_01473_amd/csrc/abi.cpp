@@ -144,12 +144,13 @@ struct Default2D {
   int bt, cpl;
 };
 Default2D default_tuning(int kind, int box, int r, int expr = 0) {
-  // expression stencils: the division costs an IEEE quotient per cell and
-  // level, gradient2d a square root and a quotient (bound by arithmetic from
-  // b_T = 2 on), per-cell weights the reading of n arrays per launch, which the
-  // deepest kernels spread over most steps (float32 at 4096 x 4000, b_T = 2 / 4:
-  // 5 points 307 / 618 GCell/s, 9-point star 161 / 273, 3x3 box 179 / 342); one
-  // tile width each (4 float32 / 2 float64 cells per lane)
+  // expression stencils: the division costs a quotient per cell and level
+  // (by the reciprocal seven operations with its check), gradient2d a square
+  // root and a quotient (bound by arithmetic from b_T = 2 on), per-cell weights
+  // the reading of n arrays per launch, which the deepest kernels spread over
+  // most steps (float32 at 4096 x 4000, b_T = 2 / 4: 5 points 307 / 618 GCell/s,
+  // 9-point star 161 / 273, 3x3 box 179 / 342); one tile width each (4 float32 /
+  // 2 float64 cells per lane)
   if (expr == s5d::EXPR_GRADIENT) return {2, kind == KIND_F64 ? 2 : 4};
   if (expr == s5d::EXPR_VARCOEF) return {4, kind == KIND_F64 ? 2 : 4};
   if (expr == s5d::EXPR_DIV) {

@@ -70,10 +70,11 @@ double ops_per_cell(const s5d_plan* p, int cpl) {
   // terms: one FMA each, or the compensated sequence (two products split
   // exactly, a two-sum and two adds: nine operations) plus its final add
   double ops = p->kind == KIND_F32_COMP ? 9.0 * (n - 1) + 3.0 : static_cast<double>(n);
-  // expressions: an IEEE quotient (about 10 float32 / 16 float64 operations);
+  // expressions: a quotient, counted as the IEEE sequence (about 10 float32 / 16
+  // float64 operations; by the reciprocal 7 with its check);
   // gradient2d: 4 differences, 4 squares, 4 sums, a square root and a
   // quotient (about 12 + 20 / 12 + 36) replacing the weighted sum; per-cell
-  // weights: one extra load per term (counted with the loads below)
+  // weights: half an operation more per term, for its weight's way through LDS
   const bool f64 = p->elem == 8;
   if (p->expr == EXPR_DIV) ops = static_cast<double>(n - 1) + (f64 ? 16.0 : 10.0);
   if (p->expr == EXPR_GRADIENT) ops = f64 ? 48.0 : 32.0;
